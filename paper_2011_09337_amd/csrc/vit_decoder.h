@@ -1012,42 +1012,34 @@ typedef void (*KernelFn)(DecodeArgs, int);
 typedef void (*BatchKernelFn)(BatchArgs, int);
 
 // Kernel instance for (K, beta, standard code, input kind, subframe traceback).
+// Without subframes the integer inputs run the kernels of vit_decoder_int.h.
 template <int K, bool SUB>
 KernelFn pick_kernel_k(int beta, bool stdc, int in) {
-  auto pick = [&](auto bt) -> KernelFn {
+  auto pick = [&](auto bt, auto sc) -> KernelFn {
     constexpr int B = decltype(bt)::value;
-    if (stdc) {
-      if (in == VIT_LLR_HARD) return dev::vit_blocked_kernel<K, B, true, VIT_LLR_HARD, SUB>;
-      return in == VIT_LLR_I8 ? dev::vit_blocked_kernel<K, B, true, VIT_LLR_I8, SUB>
-                              : dev::vit_blocked_kernel<K, B, true, VIT_LLR_F32, SUB>;
+    constexpr bool STDC = decltype(sc)::value;
+    if constexpr (SUB) {
+      if (in == VIT_LLR_HARD) return dev::vit_blocked_kernel<K, B, STDC, VIT_LLR_HARD, SUB>;
+      if (in == VIT_LLR_I8) return dev::vit_blocked_kernel<K, B, STDC, VIT_LLR_I8, SUB>;
     }
-    if (in == VIT_LLR_HARD) return dev::vit_blocked_kernel<K, B, false, VIT_LLR_HARD, SUB>;
-    return in == VIT_LLR_I8 ? dev::vit_blocked_kernel<K, B, false, VIT_LLR_I8, SUB>
-                            : dev::vit_blocked_kernel<K, B, false, VIT_LLR_F32, SUB>;
+    return in == VIT_LLR_F32 ? dev::vit_blocked_kernel<K, B, STDC, VIT_LLR_F32, SUB> : nullptr;
   };
+  auto by_std = [&](auto bt) { return stdc ? pick(bt, std::true_type{}) : pick(bt, std::false_type{}); };
   switch (beta) {
-    case 2: return pick(std::integral_constant<int, 2>{});
-    case 3: return pick(std::integral_constant<int, 3>{});
-    case 4: return pick(std::integral_constant<int, 4>{});
+    case 2: return by_std(std::integral_constant<int, 2>{});
+    case 3: return by_std(std::integral_constant<int, 3>{});
+    case 4: return by_std(std::integral_constant<int, 4>{});
   }
   return nullptr;
 }
 
+// FP32 batch kernel instance for (K, beta, standard code).
 template <int K>
-BatchKernelFn pick_batch_kernel_k(int beta, bool stdc, int in) {
-  auto pick = [&](auto bt) -> BatchKernelFn {
-    constexpr int B = decltype(bt)::value;
-    if (stdc) {
-      if (in == VIT_LLR_HARD) return dev::vit_batch_kernel<K, B, true, VIT_LLR_HARD>;
-      return in == VIT_LLR_I8 ? dev::vit_batch_kernel<K, B, true, VIT_LLR_I8> : dev::vit_batch_kernel<K, B, true, VIT_LLR_F32>;
-    }
-    if (in == VIT_LLR_HARD) return dev::vit_batch_kernel<K, B, false, VIT_LLR_HARD>;
-    return in == VIT_LLR_I8 ? dev::vit_batch_kernel<K, B, false, VIT_LLR_I8> : dev::vit_batch_kernel<K, B, false, VIT_LLR_F32>;
-  };
+BatchKernelFn pick_batch_kernel_k(int beta, bool stdc) {
   switch (beta) {
-    case 2: return pick(std::integral_constant<int, 2>{});
-    case 3: return pick(std::integral_constant<int, 3>{});
-    case 4: return pick(std::integral_constant<int, 4>{});
+    case 2: return stdc ? dev::vit_batch_kernel<K, 2, true, VIT_LLR_F32> : dev::vit_batch_kernel<K, 2, false, VIT_LLR_F32>;
+    case 3: return stdc ? dev::vit_batch_kernel<K, 3, true, VIT_LLR_F32> : dev::vit_batch_kernel<K, 3, false, VIT_LLR_F32>;
+    case 4: return stdc ? dev::vit_batch_kernel<K, 4, true, VIT_LLR_F32> : dev::vit_batch_kernel<K, 4, false, VIT_LLR_F32>;
   }
   return nullptr;
 }
@@ -1066,12 +1058,12 @@ KernelFn pick_kernel_k8(int beta, bool stdc, int in);
 KernelFn pick_kernel_sub_k8(int beta, bool stdc, int in);
 KernelFn pick_kernel_k9(int beta, bool stdc, int in);
 KernelFn pick_kernel_sub_k9(int beta, bool stdc, int in);
-BatchKernelFn pick_batch_kernel_k3(int beta, bool stdc, int in);
-BatchKernelFn pick_batch_kernel_k4(int beta, bool stdc, int in);
-BatchKernelFn pick_batch_kernel_k5(int beta, bool stdc, int in);
-BatchKernelFn pick_batch_kernel_k6(int beta, bool stdc, int in);
-BatchKernelFn pick_batch_kernel_k7(int beta, bool stdc, int in);
-BatchKernelFn pick_batch_kernel_k8(int beta, bool stdc, int in);
-BatchKernelFn pick_batch_kernel_k9(int beta, bool stdc, int in);
+BatchKernelFn pick_batch_kernel_k3(int beta, bool stdc);
+BatchKernelFn pick_batch_kernel_k4(int beta, bool stdc);
+BatchKernelFn pick_batch_kernel_k5(int beta, bool stdc);
+BatchKernelFn pick_batch_kernel_k6(int beta, bool stdc);
+BatchKernelFn pick_batch_kernel_k7(int beta, bool stdc);
+BatchKernelFn pick_batch_kernel_k8(int beta, bool stdc);
+BatchKernelFn pick_batch_kernel_k9(int beta, bool stdc);
 
 }  // namespace vit

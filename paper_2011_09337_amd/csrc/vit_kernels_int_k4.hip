@@ -1,0 +1,6 @@
+// vit_kernels_int_k4.hip -- integer kernel instances (stream and batch) for constraint length k = 4.
+#include "vit_decoder_int.h"
+
+namespace vit {
+void *pick_kernel_int_k4(int beta, bool top, int in, bool batch) { return pick_kernel_int_k<4>(beta, top, in, batch); }
+}  // namespace vit

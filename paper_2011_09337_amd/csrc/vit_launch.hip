@@ -2,11 +2,40 @@
 // occupancy-based grid size, LDS sizing and launch.
 #include "vit_decoder.h"
 #include "vit_decoder16.h"
+#include "vit_decoder_int.h"
 #include "vit_shapes.h"
 
 namespace vit {
 namespace {
 
+
+// Every generator taps the newest input (bit k-1).
+bool taps_newest(int k, int beta, const uint32_t *gen) {
+  bool t = true;
+  for (int b = 0; b < beta; ++b) t = t && ((gen[b] >> (k - 1)) & 1u);
+  return t;
+}
+
+// Every generator taps both ends of the register.
+bool taps_both_ends(int k, int beta, const uint32_t *gen) {
+  bool t = taps_newest(k, beta, gen);
+  for (int b = 0; b < beta; ++b) t = t && (gen[b] & 1u);
+  return t;
+}
+
+void *pick_kernel_int(int k, int beta, const uint32_t *gen, int in, bool batch) {
+  const bool top = taps_newest(k, beta, gen);
+  switch (k) {
+    case 3: return pick_kernel_int_k3(beta, top, in, batch);
+    case 4: return pick_kernel_int_k4(beta, top, in, batch);
+    case 5: return pick_kernel_int_k5(beta, top, in, batch);
+    case 6: return pick_kernel_int_k6(beta, top, in, batch);
+    case 7: return pick_kernel_int_k7(beta, top, in, batch);
+    case 8: return pick_kernel_int_k8(beta, top, in, batch);
+    case 9: return pick_kernel_int_k9(beta, top, in, batch);
+  }
+  return nullptr;
+}
 
 KernelFn pick_kernel(int k, int beta, bool stdc, int in, bool sub) {
   switch (k) {
@@ -177,9 +206,10 @@ hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsuppor
       return hipSuccess;
     }
   }
-  bool stdc = true;
-  for (int b = 0; b < a.beta; ++b) stdc = stdc && ((a.gen[b] >> (a.k - 1)) & 1u) && (a.gen[b] & 1u);
-  KernelFn fn = pick_kernel(a.k, a.beta, stdc, a.llr_type, a.sub_bits > 0);
+  const void *fn = a.llr_type != VIT_LLR_F32 && a.sub_bits == 0
+                       ? pick_kernel_int(a.k, a.beta, a.gen, a.llr_type, false)
+                       : reinterpret_cast<const void *>(pick_kernel(a.k, a.beta, taps_both_ends(a.k, a.beta, a.gen),
+                                                                    a.llr_type, a.sub_bits > 0));
   if (!fn) {
     *unsupported = 1;
     *why = "no kernel instance for this (k, beta)";
@@ -206,7 +236,7 @@ hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsuppor
   // 64.0 against 62.2 Gb/s; -2% to +5% for the other codes and lengths).
   int wpb = (2 * lds_wave <= t_dev.max_lds) ? 2 : 1;
   int occ = 0;
-  err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, reinterpret_cast<const void *>(fn), 64 * wpb,
+  err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, 64 * wpb,
                                                      (size_t)lds_wave * wpb);
   if (err != hipSuccess) return err;
   if (occ < 1) occ = 1;
@@ -222,14 +252,14 @@ hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsuppor
   }
   if (grid < 1) grid = 1;
   if (lds > 65536) {
-    err = hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
+    err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds);
     if (err != hipSuccess) return err;
   }
   DecodeArgs args = a;
   int words = (int)(lds_wave / 4);
   void *kargs[] = {&args, &words};
-  err = hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3((unsigned)grid), dim3(64 * wpb), kargs, lds,
+  err = hipLaunchKernel(fn, dim3((unsigned)grid), dim3(64 * wpb), kargs, lds,
                         stream);
   if (err != hipSuccess) return err;
   return hipGetLastError();
@@ -284,17 +314,17 @@ hipError_t plan_batch_launch(int k, int beta, const uint32_t *gen, int in, int m
     bl->metric_bits = kMetric16;
     return hipSuccess;
   }
-  bool stdc = true;
-  for (int b = 0; b < beta; ++b) stdc = stdc && ((gen[b] >> (k - 1)) & 1u) && (gen[b] & 1u);
-  BatchKernelFn fn = nullptr;
-  switch (k) {
-    case 3: fn = pick_batch_kernel_k3(beta, stdc, in); break;
-    case 4: fn = pick_batch_kernel_k4(beta, stdc, in); break;
-    case 5: fn = pick_batch_kernel_k5(beta, stdc, in); break;
-    case 6: fn = pick_batch_kernel_k6(beta, stdc, in); break;
-    case 7: fn = pick_batch_kernel_k7(beta, stdc, in); break;
-    case 8: fn = pick_batch_kernel_k8(beta, stdc, in); break;
-    case 9: fn = pick_batch_kernel_k9(beta, stdc, in); break;
+  const void *fn = nullptr;
+  const bool stdc = taps_both_ends(k, beta, gen);
+  if (in != VIT_LLR_F32) fn = pick_kernel_int(k, beta, gen, in, true);
+  else switch (k) {
+    case 3: fn = reinterpret_cast<const void *>(pick_batch_kernel_k3(beta, stdc)); break;
+    case 4: fn = reinterpret_cast<const void *>(pick_batch_kernel_k4(beta, stdc)); break;
+    case 5: fn = reinterpret_cast<const void *>(pick_batch_kernel_k5(beta, stdc)); break;
+    case 6: fn = reinterpret_cast<const void *>(pick_batch_kernel_k6(beta, stdc)); break;
+    case 7: fn = reinterpret_cast<const void *>(pick_batch_kernel_k7(beta, stdc)); break;
+    case 8: fn = reinterpret_cast<const void *>(pick_batch_kernel_k8(beta, stdc)); break;
+    case 9: fn = reinterpret_cast<const void *>(pick_batch_kernel_k9(beta, stdc)); break;
   }
   if (!fn) {
     *unsupported = 1;
@@ -310,15 +340,15 @@ hipError_t plan_batch_launch(int k, int beta, const uint32_t *gen, int in, int m
     return hipSuccess;
   }
   if (lds > 65536) {
-    err = hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
+    err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds);
     if (err != hipSuccess) return err;
   }
   int occ = 0;
-  err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, reinterpret_cast<const void *>(fn), 64 * wpb, lds);
+  err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, 64 * wpb, lds);
   if (err != hipSuccess) return err;
   if (occ < 1) occ = 1;
-  bl->fn = reinterpret_cast<const void *>(fn);
+  bl->fn = fn;
   bl->grid = (unsigned)(occ * t_dev.num_cu);
   bl->block = (unsigned)(64 * wpb);
   bl->lds = lds;
