@@ -298,7 +298,7 @@ def bench_batched(vit, torch, args):
     return {
         "workload": f"{len(frames)} terminated frames, n uniform in [40, 6144] ({nbits} bits), code uniform over "
                     f"{'/'.join(BATCH_CODES)}, Eb/N0 uniform in [1, 5] dB, int8 LLRs (noiseless amplitude 8); "
-                    f"one graph launch per step, autotuned shapes",
+                    f"one call per step, autotuned shapes",
         "metric_bits": 32,
         "mbps": round(nbits / (ms * 1e-3) / 1e6, 2),
         "ms_per_step": round(ms, 4),

@@ -189,10 +189,10 @@ int vit_query_geometry(const vit_code *code, int64_t n, int32_t L, int32_t v, in
 
 /* ---------------------------------------------------------------- batches
  * Many independent frames (each its own stream, Sec. III applied per frame),
- * possibly of different codes and lengths, decoded by one graph launch: one
- * persistent kernel per code (in sequence, most work per bit first) walks the
- * frames' blocks in a cost-sorted work list (longest first), wave w of W
- * taking items w, w + W, w + 2W, ...
+ * possibly of different codes and lengths, decoded in one call: a kernel writes
+ * the work list (one item per block, longest first) on the device from one
+ * record per frame, then one kernel per code (in sequence, most work per bit
+ * first) walks its items, wave w of W taking items w, w + W, w + 2W, ...
  * Results are identical, bit for bit, to decoding each frame alone with
  * vit_decode_ex and the same (L, v, v1). */
 
@@ -213,13 +213,11 @@ typedef struct {
   int32_t waves_per_block;  /* waves per workgroup, 1..4                         */
 } vit_tuning;
 
-/* A plan owns pinned host staging for work lists, a captured hipGraph that is
- * reused while the buffers and shapes stay the same, and the autotuner's
- * choices.  It never allocates device memory: the caller supplies the
- * workspace.  A plan is not thread-safe, and the batch entry points are to be
- * called from one thread at a time: two threads decoding with two plans at
- * once ended the process once (a host-side crash inside vit_decode_batch
- * whose cause is not known). */
+/* A plan owns pinned host staging for frame records, the launch shapes of the
+ * last call's codes, and the autotuner's choices.  It never allocates device
+ * memory: the caller supplies the workspace.  A plan is not thread-safe, and
+ * the batch entry points are to be called from one thread at a time (not
+ * verified with several at once). */
 typedef struct vit_plan vit_plan;
 
 int vit_plan_create(vit_plan **plan);

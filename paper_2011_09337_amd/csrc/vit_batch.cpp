@@ -3,13 +3,12 @@
 //
 // A batch is cut into blocks exactly as each frame would be on its own
 // (Sec. III of the paper, per frame).  Each block is one work item; items of
-// one code are sorted by cost (stages) so that the kernel's waves take the
-// longest first.  Per call the host writes the header (item
-// counts and run offsets per code) and the items into pinned staging memory;
-// the graph copies them into the caller's device workspace and runs one kernel
-// node per code, in sequence.  While the buffers, codes and shapes stay the
-// same the graph is reused; only its copy node and the kernel grids (sized to
-// each code's item count) are updated.
+// one code come longest first, so that the kernel's waves take the longest
+// first: the frames' middle blocks (all of L + v stages), their first blocks,
+// then their last (or only) blocks by length.  Per call the host writes one
+// record per frame into pinned staging memory and launches, on the caller's
+// stream, a kernel that writes header and items into the caller's device
+// workspace (vit_expand.hip) and one decode kernel per code, in sequence.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <string.h>
@@ -32,22 +31,11 @@ struct vit_plan {
   bool pending[2] = {false, false};
   int slot = 0;
 
-  // graph cache
-  bool have_graph = false;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-  hipGraphNode_t copy_node = nullptr;                   // the header
-  hipGraphNode_t code_copy[vit::kMaxCodes] = {};         // each code's run of work items
-  // per code: its kernel node, launch shape, arguments and current grid
-  hipGraphNode_t knode[vit::kMaxCodes] = {};
+  // launch shapes of the last call's codes and shapes
+  bool have_launch = false;
   vit::BatchLaunch bl[vit::kMaxCodes] = {};
-  vit::BatchArgs kargs[vit::kMaxCodes] = {};
-  int kwords[vit::kMaxCodes] = {};
-  unsigned kgrid[vit::kMaxCodes] = {};
+  int ncu = 0;
   struct Key {
-    const void *llr = nullptr;
-    void *out = nullptr;
-    void *ws = nullptr;
     int llr_type = -1;
     int metric_bits = -1;
     int ncodes = 0;
@@ -69,8 +57,8 @@ struct vit_plan {
 
   // host scratch reused across calls (large per-call vectors would be mmap'd
   // and page-faulted afresh every call)
-  std::vector<vit::WorkItem> sort_tmp;
-  std::vector<int64_t> sort_hist;
+  std::vector<int32_t> rank;  // per frame: its last block's place among its code's
+  std::vector<int32_t> hist;  // last blocks by length, all codes
   std::vector<std::pair<int64_t, int64_t>> out_ranges;
 };
 
@@ -260,21 +248,95 @@ int check_frames_plan(vit_plan *plan, const vit_code *codes, int32_t ncodes, con
   return check_frames(codes, ncodes, frames, nframes, llr_count, llr_type, out_bytes, plan->out_ranges.data());
 }
 
-// build_items with the plan's sort buffers, sized for the largest run and cost
-int64_t build_items_plan(vit_plan *plan, const vit_code *codes, int32_t ncodes, const vit_frame *frames,
-                         int32_t nframes, const vit_tuning *shape, int elem_bytes, WorkItem *items, int32_t *header,
-                         int64_t *max_stages) {
-  int64_t counts[kMaxCodes] = {0};
-  for (int32_t f = 0; f < nframes; ++f) counts[frames[f].code_id] += (frames[f].n + shape[frames[f].code_id].L - 1) / shape[frames[f].code_id].L;
-  int64_t run = 0, cost = 0;
-  for (int c = 0; c < ncodes; ++c) {
-    run = std::max(run, counts[c]);
-    cost = std::max(cost, (int64_t)shape[c].L + shape[c].v);
+// A record covers at most this many blocks (eight lanes write its items).
+constexpr int64_t kRecordBlocks = 256;
+
+// Blocks per code and records for these frames under these shapes.
+int64_t count_records(int32_t ncodes, const vit_frame *frames, int32_t nframes, const vit_tuning *shape,
+                      int64_t *counts) {
+  int64_t records = 0;
+  for (int c = 0; c < ncodes; ++c) counts[c] = 0;
+  for (int32_t f = 0; f < nframes; ++f) {
+    const int64_t L = shape[frames[f].code_id].L, nb = (frames[f].n + L - 1) / L;
+    counts[frames[f].code_id] += nb;
+    records += nb <= kRecordBlocks ? 1 : (nb + kRecordBlocks - 1) / kRecordBlocks;
   }
-  plan->sort_tmp.resize((size_t)run);
-  plan->sort_hist.resize((size_t)cost + 2);
-  return build_items(codes, ncodes, frames, nframes, shape, elem_bytes, items, header, max_stages,
-                     plan->sort_tmp.data(), plan->sort_hist.data());
+  return records;
+}
+
+// The frames' records, and every code's item range in *a.  Last blocks are
+// ranked by a stable counting sort on their length, longest first.
+void write_records(vit_plan *plan, const vit_code *codes, int32_t ncodes, const vit_frame *frames, int32_t nframes,
+                   const vit_tuning *shape, int elem_bytes, const int64_t *counts, vit::FrameRecord *rec,
+                   vit::ExpandArgs *a) {
+  int64_t hist_at[kMaxCodes], hist_len = 0;
+  for (int c = 0; c < ncodes; ++c) {
+    a->L[c] = shape[c].L;
+    a->v1[c] = shape[c].v1 < 0 ? shape[c].v / 2 : shape[c].v1;
+    a->v2[c] = shape[c].v - a->v1[c];
+    a->tail[c] = codes[c].k - 1;
+    hist_at[c] = hist_len;
+    hist_len += (int64_t)shape[c].L + shape[c].v + 1;
+  }
+  vit::alloc_checkpoint();
+  plan->hist.assign((size_t)hist_len, 0);
+  plan->rank.resize((size_t)nframes);
+  int64_t middle[kMaxCodes] = {0}, front[kMaxCodes] = {0}, last[kMaxCodes];
+  for (int32_t f = 0; f < nframes; ++f) {
+    const vit_frame &fr = frames[f];
+    const int c = fr.code_id;
+    const int64_t L = a->L[c], nb = (fr.n + L - 1) / L, cs = (nb - 1) * L;
+    const int64_t N = fr.n + (fr.terminated ? a->tail[c] : 0);
+    const int64_t s = cs - a->v1[c] > 0 ? cs - a->v1[c] : 0, e = fr.n + a->v2[c] < N ? fr.n + a->v2[c] : N;
+    plan->rank[f] = (int32_t)(e - s);  // its length until the places are known
+    ++plan->hist[(size_t)(hist_at[c] + e - s)];
+    if (nb > 1) {
+      ++front[c];
+      middle[c] += nb - 2;
+    }
+  }
+  int64_t at = 0;
+  for (int c = 0; c < ncodes; ++c) {
+    a->first[c] = (int32_t)at;
+    a->count[c] = (int32_t)counts[c];
+    // the run: middle blocks, first blocks, last blocks (longest first)
+    const int64_t nmid = middle[c], nfront = front[c];
+    middle[c] = at;
+    front[c] = at + nmid;
+    last[c] = at + nmid + nfront;
+    int64_t place = last[c];
+    for (int64_t len = (int64_t)shape[c].L + shape[c].v; len >= 0; --len) {
+      int32_t &h = plan->hist[(size_t)(hist_at[c] + len)];
+      const int32_t k = h;
+      h = (int32_t)place;
+      place += k;
+    }
+    at += counts[c];
+  }
+  for (int32_t f = 0; f < nframes; ++f) {
+    const vit_frame &fr = frames[f];
+    const int c = fr.code_id;
+    const int64_t nb = (fr.n + a->L[c] - 1) / a->L[c];
+    vit::FrameRecord r;
+    r.llr_off = fr.llr_off * elem_bytes;
+    r.out_off = fr.out_off;
+    r.n = (int32_t)fr.n;
+    r.nblocks = (int32_t)nb;
+    r.code = (int16_t)c;
+    r.terminated = (int16_t)fr.terminated;
+    r.last = plan->hist[(size_t)(hist_at[c] + plan->rank[f])]++;
+    r.front = r.middle = r.last;
+    if (nb > 1) {
+      r.front = (int32_t)front[c]++;
+      r.middle = (int32_t)middle[c];
+      middle[c] += nb - 2;
+    }
+    for (int64_t b = 0; b < nb; b += kRecordBlocks) {
+      r.b0 = (int32_t)b;
+      r.b1 = (int32_t)std::min(nb, b + kRecordBlocks);
+      *rec++ = r;
+    }
+  }
 }
 
 int resolve_shapes(vit_plan *plan, const vit_code *codes, int32_t ncodes, const vit_frame *frames, int32_t nframes,
@@ -315,31 +377,6 @@ int ensure_staging(vit_plan *p, int slot, size_t bytes) {
   return VIT_OK;
 }
 
-// The bytes of code c's work items in the staging area and the workspace (a
-// code without items copies the header again, a copy of no bytes being no
-// graph node).
-struct CodeCopy {
-  void *dst;
-  const void *src;
-  size_t bytes;
-};
-CodeCopy code_copy_range(const int32_t *header, int c, void *workspace, const void *stg) {
-  const int64_t count = header[kMaxCodes + c];
-  if (count == 0) return {workspace, stg, kHeaderBytes};
-  const size_t off = kHeaderBytes + (size_t)header[2 * kMaxCodes + c] * sizeof(WorkItem);
-  return {(char *)workspace + off, (const char *)stg + off, (size_t)count * sizeof(WorkItem)};
-}
-
-void drop_graph(vit_plan *p) {
-  if (p->exec) (void)hipGraphExecDestroy(p->exec);
-  if (p->graph) (void)hipGraphDestroy(p->graph);
-  p->exec = nullptr;
-  p->graph = nullptr;
-  p->copy_node = nullptr;
-  for (auto &n : p->code_copy) n = nullptr;
-  p->have_graph = false;
-}
-
 }  // namespace
 
 extern "C" {
@@ -361,7 +398,6 @@ void vit_plan_destroy(vit_plan *plan) {
     }
     if (plan->staging[i]) (void)hipHostFree(plan->staging[i]);
   }
-  drop_graph(plan);
   delete plan;
 }
 
@@ -414,169 +450,105 @@ static int decode_batch_impl(vit_plan *plan, const vit_code *codes, int32_t ncod
   }
 
   const int elem = llr_type == VIT_LLR_F32 ? 4 : 1;
-  const int64_t total = build_items(codes, ncodes, frames, nframes, shape, elem, nullptr, nullptr, nullptr, nullptr, nullptr);
+  int64_t counts[kMaxCodes];
+  const int64_t nrecords = count_records(ncodes, frames, nframes, shape, counts);
+  int64_t total = 0;
+  for (int c = 0; c < ncodes; ++c) total += counts[c];
   const size_t need = kHeaderBytes + (size_t)total * sizeof(WorkItem);
   if (workspace_bytes < need)
     return api_fail(VIT_EINVAL, "workspace of %zu bytes, %zu needed", workspace_bytes, need);
   if (total >= ((int64_t)1 << 31)) return api_fail(VIT_EUNSUPPORTED, "too many blocks");
 
-  // the staging slot's previous copy must have run before it is rewritten
-  const int slot = plan->slot;
-  hipError_t he;
-  if (plan->pending[slot]) {
-    he = hipEventSynchronize(plan->done[slot]);
-    if (he != hipSuccess) return vit::api_fail_hip(he, "hipEventSynchronize");
-    plan->pending[slot] = false;
-  }
-  st = ensure_staging(plan, slot, need);
-  if (st) return st;
-  char *stg = (char *)plan->staging[slot];
-  int32_t *header = (int32_t *)stg;
-  memset(header, 0, kHeaderBytes);
-  int64_t max_stages[kMaxCodes];
-  build_items_plan(plan, codes, ncodes, frames, nframes, shape, elem, (WorkItem *)(stg + kHeaderBytes), header,
-                   max_stages);
-
+  // launch shapes (LDS sized for the longest block a shape can produce),
+  // kept while codes and shapes stay the same; nothing is launched or kept
+  // unless every code has one
   int dev = 0;
-  he = hipGetDevice(&dev);
+  hipError_t he = hipGetDevice(&dev);
   if (he != hipSuccess) return vit::api_fail_hip(he, "hipGetDevice");
-
-  int ncu = 256;
-  he = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-  if (he != hipSuccess) return vit::api_fail_hip(he, "hipDeviceGetAttribute");
-
-  // graph: reuse while buffers, codes and shapes are unchanged
   vit_plan::Key key;
-  key.llr = llr;
-  key.out = out;
-  key.ws = workspace;
   key.llr_type = llr_type;
   key.metric_bits = plan->metric_bits;
   key.ncodes = ncodes;
   key.dev = dev;
-  bool same = plan->have_graph && plan->key.llr == llr && plan->key.out == out && plan->key.ws == workspace &&
-              plan->key.llr_type == llr_type && plan->key.metric_bits == plan->metric_bits &&
+  bool same = plan->have_launch && plan->key.llr_type == llr_type && plan->key.metric_bits == plan->metric_bits &&
               plan->key.ncodes == ncodes && plan->key.dev == dev;
   for (int c = 0; c < ncodes; ++c) {
     key.codes[c] = codes[c];
     key.tune[c] = shape[c];
     if (same) same = same_code(plan->key.codes[c], codes[c]) && same_tuning(plan->key.tune[c], shape[c]);
   }
-  auto grid_for = [&](int c) -> unsigned {
-    return vit::batch_launch_grid(plan->bl[c], header[kMaxCodes + c], (int64_t)shape[c].L + shape[c].v, ncu);
-  };
   if (!same) {
-    // The old graph goes first: if planning or building fails below, no
-    // later call may take the reuse branch with a half-updated plan.  The
-    // launch shapes are planned aside and kept only with a complete graph.
-    drop_graph(plan);
-    // launch shapes (LDS sized for the longest block a shape can produce)
-    vit::BatchLaunch bl[kMaxCodes];
+    plan->have_launch = false;
     for (int c = 0; c < ncodes; ++c) {
       int unsupported = 0;
       const char *why = "";
       he = vit::plan_batch_launch(codes[c].k, codes[c].beta, codes[c].gen, llr_type, plan->metric_bits,
-                                  (int64_t)shape[c].L + shape[c].v, shape[c].waves_per_block, &bl[c], &unsupported,
-                                  &why);
+                                  (int64_t)shape[c].L + shape[c].v, shape[c].waves_per_block, &plan->bl[c],
+                                  &unsupported, &why);
       if (he != hipSuccess) return vit::api_fail_hip(he, "batch launch planning");
       if (unsupported) return api_fail(VIT_EUNSUPPORTED, "code %d: %s", c, why);
     }
-    he = hipGraphCreate(&plan->graph, 0);
-    if (he != hipSuccess) return vit::api_fail_hip(he, "hipGraphCreate");
-    he = hipGraphAddMemcpyNode1D(&plan->copy_node, plan->graph, nullptr, 0, workspace, stg, kHeaderBytes,
-                                 hipMemcpyHostToDevice);
-    if (he != hipSuccess) return vit::api_fail_hip(he, "hipGraphAddMemcpyNode1D");
-    // one kernel node per code, run one after another, the code with the
-    // most work per bit (states x rate) first: measured faster than running
-    // them side by side.  Each code's work items are copied by a node of
-    // their own, the copies chained in launch order, so that a kernel waits
-    // only for its own items and the later codes' copies run during the
-    // earlier kernels.
-    int order[kMaxCodes];
-    vit::batch_code_order(codes, ncodes, order);
-    hipGraphNode_t prev = nullptr, prev_copy = plan->copy_node;
-    for (int oi = 0; oi < ncodes; ++oi) {
-      const int c = order[oi];
-      {
-        const CodeCopy cc = code_copy_range(header, c, workspace, stg);
-        he = hipGraphAddMemcpyNode1D(&plan->code_copy[c], plan->graph, &prev_copy, 1, cc.dst, cc.src, cc.bytes,
-                                     hipMemcpyHostToDevice);
-        if (he != hipSuccess) return vit::api_fail_hip(he, "hipGraphAddMemcpyNode1D");
-        prev_copy = plan->code_copy[c];
-      }
-      vit::BatchArgs &args = plan->kargs[c];
-      args.llr = llr;
-      args.out = out;
-      args.header = (int32_t *)workspace;
-      args.items = (const WorkItem *)((char *)workspace + kHeaderBytes);
-      args.code_index = c;
-      for (int b = 0; b < 4; ++b) args.gen[b] = b < codes[c].beta ? codes[c].gen[b] : 0u;
-      plan->kwords[c] = bl[c].lds_words_per_wave;
-      void *kargs[] = {&args, &plan->kwords[c]};
-      plan->kgrid[c] = vit::batch_launch_grid(bl[c], header[kMaxCodes + c], (int64_t)shape[c].L + shape[c].v, ncu);
-      hipKernelNodeParams kp;
-      memset(&kp, 0, sizeof(kp));
-      kp.func = const_cast<void *>(bl[c].fn);
-      kp.gridDim = dim3(plan->kgrid[c]);
-      kp.blockDim = dim3(bl[c].block);
-      kp.sharedMemBytes = (unsigned)bl[c].lds;
-      kp.kernelParams = kargs;
-      kp.extra = nullptr;
-      hipGraphNode_t kn;
-      hipGraphNode_t deps[2] = {plan->code_copy[c], prev};
-      he = hipGraphAddKernelNode(&kn, plan->graph, deps, prev ? 2 : 1, &kp);
-      if (he != hipSuccess) return vit::api_fail_hip(he, "hipGraphAddKernelNode");
-      plan->knode[c] = kn;
-      prev = kn;
-    }
-    he = hipGraphInstantiate(&plan->exec, plan->graph, nullptr, nullptr, 0);
-    if (he != hipSuccess) {
-      drop_graph(plan);
-      return vit::api_fail_hip(he, "hipGraphInstantiate");
-    }
-    for (int c = 0; c < ncodes; ++c) plan->bl[c] = bl[c];
+    he = hipDeviceGetAttribute(&plan->ncu, hipDeviceAttributeMultiprocessorCount, dev);
+    if (he != hipSuccess) return vit::api_fail_hip(he, "hipDeviceGetAttribute");
     plan->key = key;
-    plan->have_graph = true;
-  } else {
-    he = hipGraphExecMemcpyNodeSetParams1D(plan->exec, plan->copy_node, workspace, stg, kHeaderBytes,
-                                           hipMemcpyHostToDevice);
-    if (he != hipSuccess) return vit::api_fail_hip(he, "hipGraphExecMemcpyNodeSetParams1D");
-    for (int c = 0; c < ncodes; ++c) {
-      const CodeCopy cc = code_copy_range(header, c, workspace, stg);
-      he = hipGraphExecMemcpyNodeSetParams1D(plan->exec, plan->code_copy[c], cc.dst, cc.src, cc.bytes,
-                                             hipMemcpyHostToDevice);
-      if (he != hipSuccess) return vit::api_fail_hip(he, "hipGraphExecMemcpyNodeSetParams1D");
-    }
-    // the item counts change from call to call: resize the dispatcher-refilled grids
-    for (int c = 0; c < ncodes; ++c) {
-      const unsigned g = grid_for(c);
-      if (g == plan->kgrid[c]) continue;
-      void *kargs[] = {&plan->kargs[c], &plan->kwords[c]};
-      hipKernelNodeParams kp;
-      memset(&kp, 0, sizeof(kp));
-      kp.func = const_cast<void *>(plan->bl[c].fn);
-      kp.gridDim = dim3(g);
-      kp.blockDim = dim3(plan->bl[c].block);
-      kp.sharedMemBytes = (unsigned)plan->bl[c].lds;
-      kp.kernelParams = kargs;
-      kp.extra = nullptr;
-      he = hipGraphExecKernelNodeSetParams(plan->exec, plan->knode[c], &kp);
-      if (he != hipSuccess) return vit::api_fail_hip(he, "hipGraphExecKernelNodeSetParams");
-      plan->kgrid[c] = g;
-    }
+    plan->have_launch = true;
   }
-  he = hipGraphLaunch(plan->exec, (hipStream_t)stream);
-  if (he != hipSuccess) return vit::api_fail_hip(he, "hipGraphLaunch");
+
+  // the staging slot's previous records must have been read before it is rewritten
+  const int slot = plan->slot;
+  if (plan->pending[slot]) {
+    he = hipEventSynchronize(plan->done[slot]);
+    if (he != hipSuccess) return vit::api_fail_hip(he, "hipEventSynchronize");
+    plan->pending[slot] = false;
+  }
+  st = ensure_staging(plan, slot, (size_t)nrecords * sizeof(vit::FrameRecord));
+  if (st) return st;
+  vit::ExpandArgs ex;
+  memset(&ex, 0, sizeof(ex));
+  ex.records = (const vit::FrameRecord *)plan->staging[slot];
+  ex.nrecords = nrecords;
+  ex.header = (int32_t *)workspace;
+  ex.items = (WorkItem *)((char *)workspace + kHeaderBytes);
+  write_records(plan, codes, ncodes, frames, nframes, shape, elem, counts, (vit::FrameRecord *)plan->staging[slot],
+                &ex);
+  he = vit::launch_expand(ex, (hipStream_t)stream);
+  if (he != hipSuccess) return vit::api_fail_hip(he, "work list kernel launch");
   if (!plan->done[slot]) {
     // a timing event: on this runtime recording one costs about a quarter
     // of recording an event with timing disabled
     he = hipEventCreate(&plan->done[slot]);
     if (he != hipSuccess) return vit::api_fail_hip(he, "hipEventCreate");
   }
+  // (the records are read by the first kernel alone: once it is done the slot
+  // can be rewritten)
   he = hipEventRecord(plan->done[slot], (hipStream_t)stream);
   if (he != hipSuccess) return vit::api_fail_hip(he, "hipEventRecord");
   plan->pending[slot] = true;
   plan->slot = slot ^ 1;
+
+  // one kernel per code, one after another, the code with the most work per
+  // bit (states x rate) first: measured faster than running them side by side
+  int order[kMaxCodes];
+  vit::batch_code_order(codes, ncodes, order);
+  for (int oi = 0; oi < ncodes; ++oi) {
+    const int c = order[oi];
+    if (counts[c] == 0) continue;
+    vit::BatchArgs args;
+    args.llr = llr;
+    args.out = out;
+    args.header = (int32_t *)workspace;
+    args.items = (const WorkItem *)((char *)workspace + kHeaderBytes);
+    args.code_index = c;
+    for (int b = 0; b < 4; ++b) args.gen[b] = b < codes[c].beta ? codes[c].gen[b] : 0u;
+    int words = plan->bl[c].lds_words_per_wave;
+    void *kargs[] = {&args, &words};
+    const unsigned grid = vit::batch_launch_grid(plan->bl[c], counts[c], (int64_t)shape[c].L + shape[c].v, plan->ncu);
+    he = hipLaunchKernel(plan->bl[c].fn, dim3(grid), dim3(plan->bl[c].block), kargs, plan->bl[c].lds,
+                         (hipStream_t)stream);
+    if (he != hipSuccess) return vit::api_fail_hip(he, "batch kernel launch");
+  }
+  he = hipGetLastError();
+  if (he != hipSuccess) return vit::api_fail_hip(he, "batch kernel launch");
   return VIT_OK;
 }
 

@@ -53,6 +53,27 @@ struct WorkItem {
 constexpr int kMaxCodes = 8;
 constexpr size_t kHeaderBytes = 256;
 
+// One frame of a batch, or blocks [b0, b1) of a long one, as the expansion
+// kernel (vit_expand.hip) reads it: the places of its blocks' items in the
+// item array.
+struct FrameRecord {
+  int64_t llr_off, out_off;  // bytes
+  int32_t n, nblocks;
+  int16_t code, terminated;
+  int32_t b0, b1;
+  int32_t front, middle, last;  // block 0, block 1 (the others behind it), the last block (also an only block)
+};
+struct ExpandArgs {
+  const FrameRecord *records;  // pinned host memory
+  int64_t nrecords;
+  int32_t *header;
+  WorkItem *items;
+  int32_t L[kMaxCodes], v1[kMaxCodes], v2[kMaxCodes], tail[kMaxCodes];  // tail: k - 1
+  int32_t count[kMaxCodes], first[kMaxCodes];                          // items per code, place of its first
+};
+// Write a batch's header and work items on the device.
+hipError_t launch_expand(const ExpandArgs &a, hipStream_t stream);
+
 // Kernel arguments of a batched decode for one code.
 struct BatchArgs {
   const void *llr;           // device, the batch's LLR buffer
