@@ -34,7 +34,6 @@ struct vit_plan {
   // launch shapes of the last call's codes and shapes
   bool have_launch = false;
   vit::BatchLaunch bl[vit::kMaxCodes] = {};
-  int ncu = 0;
   struct Key {
     int llr_type = -1;
     int metric_bits = -1;
@@ -483,13 +482,11 @@ static int decode_batch_impl(vit_plan *plan, const vit_code *codes, int32_t ncod
       int unsupported = 0;
       const char *why = "";
       he = vit::plan_batch_launch(codes[c].k, codes[c].beta, codes[c].gen, llr_type, plan->metric_bits,
-                                  (int64_t)shape[c].L + shape[c].v, shape[c].waves_per_block, &plan->bl[c],
-                                  &unsupported, &why);
+                                  (int64_t)shape[c].L + shape[c].v, vit::traced_stages(shape[c]),
+                                  shape[c].waves_per_block, &plan->bl[c], &unsupported, &why);
       if (he != hipSuccess) return vit::api_fail_hip(he, "batch launch planning");
       if (unsupported) return api_fail(VIT_EUNSUPPORTED, "code %d: %s", c, why);
     }
-    he = hipDeviceGetAttribute(&plan->ncu, hipDeviceAttributeMultiprocessorCount, dev);
-    if (he != hipSuccess) return vit::api_fail_hip(he, "hipDeviceGetAttribute");
     plan->key = key;
     plan->have_launch = true;
   }
@@ -528,6 +525,8 @@ static int decode_batch_impl(vit_plan *plan, const vit_code *codes, int32_t ncod
 
   // one kernel per code, one after another, the code with the most work per
   // bit (states x rate) first: measured faster than running them side by side
+  bool whole[kMaxCodes];
+  vit::frames_of_whole_words(ncodes, frames, nframes, whole);
   int order[kMaxCodes];
   vit::batch_code_order(codes, ncodes, order);
   for (int oi = 0; oi < ncodes; ++oi) {
@@ -542,9 +541,9 @@ static int decode_batch_impl(vit_plan *plan, const vit_code *codes, int32_t ncod
     for (int b = 0; b < 4; ++b) args.gen[b] = b < codes[c].beta ? codes[c].gen[b] : 0u;
     int words = plan->bl[c].lds_words_per_wave;
     void *kargs[] = {&args, &words};
-    const unsigned grid = vit::batch_launch_grid(plan->bl[c], counts[c], (int64_t)shape[c].L + shape[c].v, plan->ncu);
-    he = hipLaunchKernel(plan->bl[c].fn, dim3(grid), dim3(plan->bl[c].block), kargs, plan->bl[c].lds,
-                         (hipStream_t)stream);
+    const vit::BatchGrid g =
+        vit::batch_grid_for(plan->bl[c], counts[c], (int64_t)shape[c].L + shape[c].v, whole[c]);
+    he = hipLaunchKernel(g.fn, dim3(g.grid), dim3(g.block), kargs, g.lds, (hipStream_t)stream);
     if (he != hipSuccess) return vit::api_fail_hip(he, "batch kernel launch");
   }
   he = hipGetLastError();

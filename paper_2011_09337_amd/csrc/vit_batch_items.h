@@ -31,6 +31,15 @@ int check_frames(const vit_code *codes, int32_t ncodes, const vit_frame *frames,
 int64_t build_items(const vit_code *codes, int32_t ncodes, const vit_frame *frames, int32_t nframes,
                     const vit_tuning *shape, int elem_bytes, WorkItem *items, int32_t *header, int64_t *max_stages,
                     WorkItem *tmp, int64_t *hist);
+// Most stages from a block's first core bit to its window's end.
+inline int64_t traced_stages(const vit_tuning &t) { return (int64_t)t.L + (t.v1 < 0 ? t.v - t.v / 2 : t.v - t.v1); }
+// Per code: does every frame hold at least 4 LLRs?  (Only an open frame of one
+// bit may not.)
+inline void frames_of_whole_words(int32_t ncodes, const vit_frame *frames, int32_t nframes, bool *whole) {
+  for (int c = 0; c < ncodes; ++c) whole[c] = true;
+  for (int32_t f = 0; f < nframes; ++f)
+    if (frames[f].n == 1 && !frames[f].terminated) whole[frames[f].code_id] = false;
+}
 // Launch order of the codes' kernels: most work per bit (states x rate) first.
 void batch_code_order(const vit_code *codes, int32_t ncodes, int *order);
 

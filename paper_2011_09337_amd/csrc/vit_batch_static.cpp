@@ -97,9 +97,8 @@ int decode_batch_static_impl(const vit_code *codes, int32_t ncodes, const vit_fr
     g_dev_scratch[dev] = p;
   }
   uint8_t *ws = (uint8_t *)g_dev_scratch[dev];
-  int ncu = 256;
-  he = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-  if (he != hipSuccess) return vit::api_fail_hip(he, "hipDeviceGetAttribute");
+  bool whole[vit::kMaxCodes];
+  vit::frames_of_whole_words(ncodes, frames, nframes, whole);
 
   // plan every code's launch before any device work, so that an unsupported
   // shape leaves the device untouched
@@ -108,8 +107,8 @@ int decode_batch_static_impl(const vit_code *codes, int32_t ncodes, const vit_fr
     int unsupported = 0;
     const char *why = "";
     he = vit::plan_batch_launch(codes[c].k, codes[c].beta, codes[c].gen, llr_type, vit::kMetricAuto,
-                                (int64_t)shape[c].L + shape[c].v, shape[c].waves_per_block, &bl[c], &unsupported,
-                                &why);
+                                (int64_t)shape[c].L + shape[c].v, vit::traced_stages(shape[c]),
+                                shape[c].waves_per_block, &bl[c], &unsupported, &why);
     if (he != hipSuccess) return vit::api_fail_hip(he, "batch launch planning");
     if (unsupported) return api_fail(VIT_EUNSUPPORTED, "code %d: %s", c, why);
   }
@@ -135,9 +134,9 @@ int decode_batch_static_impl(const vit_code *codes, int32_t ncodes, const vit_fr
     for (int b = 0; b < 4; ++b) args.gen[b] = b < codes[c].beta ? codes[c].gen[b] : 0u;
     int words = bl[c].lds_words_per_wave;
     void *kargs[] = {&args, &words};
-    const unsigned grid =
-        vit::batch_launch_grid(bl[c], header[vit::kMaxCodes + c], (int64_t)shape[c].L + shape[c].v, ncu);
-    he = hipLaunchKernel(bl[c].fn, dim3(grid), dim3(bl[c].block), kargs, bl[c].lds, (hipStream_t)stream);
+    const vit::BatchGrid g =
+        vit::batch_grid_for(bl[c], header[vit::kMaxCodes + c], (int64_t)shape[c].L + shape[c].v, whole[c]);
+    he = hipLaunchKernel(g.fn, dim3(g.grid), dim3(g.block), kargs, g.lds, (hipStream_t)stream);
     if (he != hipSuccess) return vit::api_fail_hip(he, "batch kernel launch");
   }
   he = hipGetLastError();

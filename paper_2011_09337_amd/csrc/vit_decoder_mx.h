@@ -1,0 +1,703 @@
+// vit_decoder_mx.h -- integer decoder on the matrix cores, for int8 and
+// hard-decision inputs with many blocks, on gfx950: device templates,
+// instantiated per constraint length (5 <= k <= 9) in vit_kernels_mx_k*.hip.
+//
+// The recursion is that of vit_decoder_int.h (rotating slots, metrics that
+// carry their ancestor's tag in the low P = k-1 bits, o = max(o + x, partner's
+// o - x)).  Here one wave decodes NB blocks at once (64, 32, 16, 8, 4 for
+// k = 5..9), 1024 slots in 16 registers, and both additions of a stage are
+// matrix instructions with the metrics as the accumulator:
+//
+//   v_mfma_*_16x16x4 (4 blocks): D[b][row, col] = A_b[row, :] . B_b[:, col] + C
+//
+//  * A is a stage's LLRs (the four products are the code's outputs), B the
+//    signs of each slot's branch times 2^P: one instruction adds the branch
+//    that stays in the slot, another the branch that leaves for the partner's
+//    slot, 32 matrix-pipe cycles each, and both run beside the vector work of
+//    the SIMD's other wave.  What is left for the vector unit is one max per
+//    slot and stage, and two instructions per period for the tags: 4 issue
+//    cycles per 64 slots instead of 8 and a crossbar fetch.
+//  * Slot bits 0..3 are the lanes of a row of 16 (col: lane xors 1, 2, 7, 8,
+//    which DPP reads inside the max); bits 4, 5 are the instruction's blocks b
+//    and bits 6, 7 the register within a row quad: partners in registers, no
+//    exchange at all.  The other row, quad and b indices number the blocks
+//    (tau).  A row that carries slot bits (k = 8, 9) puts their branch signs on
+//    its LLRs.
+//  * k <= 7: int8 LLRs straight from memory, 32-bit integer sums.  k = 8, 9
+//    need 2^P > 64, more than a byte's sign factor: fp16 operands, fp32 sums
+//    kept as 2^23 + 2^22 + integer, whose bits count like the integer's (the
+//    tags and the max work on the bits); the metrics are taken back towards 0
+//    every RENORM stages.
+//  * Blocks of different lengths share a wave: all end at the last stage of
+//    the last body; a block is set to its start metrics at its first stage.
+//  * Survivor words as in vit_decoder_int.h: those of a block's first eight
+//    traced bodies in 128 registers of their own, the others in LDS,
+//    [slot][tau].  The traceback runs one lane per block, one dependent LDS read
+//    per period.
+//
+// What bounds it: a wave alone on a SIMD takes 92 ns per stage (k = 7, 16 blocks:
+// the two matrix instructions one after the other, their latency, then 16 max);
+// two waves overlap the one's matrix with the other's vector work, 140 ns for
+// both; registers and LDS hold no third.  Measured, one-block kernel / here:
+// K=7 r1/2, 2^24 int8 bits, v = 35: L = 256 210 / 91 us, L = 512 (one wave per
+// SIMD by LDS; without the register bodies two a CU and 212 us) 198 / 121;
+// K=7 r1/3, L = 256 213 / 102; K=9 r1/2, 2^22 bits, L = 256, v = 64 236 / 104;
+// K=5 r1/2, 2^24 bits, L = 256 204 / 42.
+#pragma once
+
+#include "vit_decoder_int.h"
+#include "vit_internal.h"
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+namespace vit {
+namespace devm {
+
+using devi::hard_to_pm1;
+using devi::max_i;
+
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kKept = 8;  // bodies whose survivors a wave keeps in registers
+
+template <int K, int BETA>
+struct ShapeM {
+  static constexpr int P = K - 1;
+  static constexpr int S = 1 << P;
+  static constexpr int BB = P - 4 < 2 ? P - 4 : 2;  // slot bits in b
+  static constexpr int IB = P - 4 - BB;             // slot bits in the quad's register
+  static constexpr int NB = 64 >> (BB + IB);        // blocks per wave
+  static constexpr int NCLS = NB / 4;               // blocks per lane
+  static constexpr int NG = 32 / P;                 // periods per body
+  static constexpr int BODY = P * NG;
+  static constexpr int BYTES = P * BETA;            // LLR bytes of a period
+  static constexpr int FULL = BYTES / 4, REM = BYTES % 4;
+  static constexpr int WORDS = FULL + (REM ? 1 : 0);
+  static constexpr bool F16 = P > 6;
+  // Periods between an LLR load and its use (a period takes about half a
+  // microsecond), limited by registers.
+  static constexpr int LOOK = NG * WORDS <= 16 ? NG : NG < 3 ? NG : 3;
+  static constexpr int NR = kKept;  // kept bodies whose survivors stay in registers, the first of a block
+  // Stages between two renormalisations of the fp32 sums, whole periods: the
+  // spread 2^8 P beta + 1, and 2^7 beta a stage, stay below 2^22 / 2^P.
+  static constexpr int kRoom = ((1 << 22) >> P) - 1 - 256 * P * BETA;
+  static constexpr int RENORM = kRoom / (128 * BETA) >= BODY ? BODY : kRoom / (128 * BETA) >= 2 * P ? 2 * P : P;
+  static_assert(!F16 || kRoom >= 128 * BETA * RENORM, "fp32 sums leave their binade");
+};
+
+typedef const __attribute__((address_space(1))) uint8_t *gin_t;
+typedef __attribute__((address_space(1))) uint8_t *gout_t;
+typedef uint32_t una32 __attribute__((aligned(1)));
+typedef const __attribute__((address_space(1))) una32 *gword_t;
+
+// What lane tau knows of block tau.
+struct Blk {
+  const uint8_t *llr;  // the window's first LLR
+  uint8_t *out;        // the byte of the core's first bit
+  int before;          // LLR bytes of the frame before the window (at most 2^20 counted)
+  int M;               // stages of the window
+  int core, ncore;     // first core bit within the window, core bits
+  bool known, zero, emit;  // starts in state 0; ends in state 0; its bytes are written
+};
+
+// Survivor words of the first kept bodies: v128..v255, 16 registers a body,
+// moved by asm that names them.  The kernels are compiled for 128 vector
+// registers (amdgpu_num_vgpr: the compiler cannot allocate the others) and
+// claim all 256 by naming v255 once as overwritten.  (As C++ values the words
+// are copied at every branch, and spill.)
+#define VITM_KEEP16(N0, N1, N2, N3, N4, N5, N6, N7, N8, N9, N10, N11, N12, N13, N14, N15)                            \
+  asm volatile("v_mov_b32 v" #N0 ", %0\n\tv_mov_b32 v" #N1 ", %1\n\tv_mov_b32 v" #N2 ", %2\n\tv_mov_b32 v" #N3        \
+               ", %3\n\tv_mov_b32 v" #N4 ", %4\n\tv_mov_b32 v" #N5 ", %5\n\tv_mov_b32 v" #N6 ", %6\n\tv_mov_b32 v" #N7 \
+               ", %7\n\tv_mov_b32 v" #N8 ", %8\n\tv_mov_b32 v" #N9 ", %9\n\tv_mov_b32 v" #N10 ", %10\n\tv_mov_b32 v"    \
+               #N11 ", %11\n\tv_mov_b32 v" #N12 ", %12\n\tv_mov_b32 v" #N13 ", %13\n\tv_mov_b32 v" #N14              \
+               ", %14\n\tv_mov_b32 v" #N15 ", %15" ::"v"(d[0]), "v"(d[1]), "v"(d[2]), "v"(d[3]), "v"(d[4]),         \
+               "v"(d[5]), "v"(d[6]), "v"(d[7]), "v"(d[8]), "v"(d[9]), "v"(d[10]), "v"(d[11]), "v"(d[12]),          \
+               "v"(d[13]), "v"(d[14]), "v"(d[15]))
+#define VITM_KEPT16(N0, N1, N2, N3, N4, N5, N6, N7, N8, N9, N10, N11, N12, N13, N14, N15)                            \
+  asm volatile("v_mov_b32 %0, v" #N0 "\n\tv_mov_b32 %1, v" #N1 "\n\tv_mov_b32 %2, v" #N2 "\n\tv_mov_b32 %3, v" #N3   \
+               "\n\tv_mov_b32 %4, v" #N4 "\n\tv_mov_b32 %5, v" #N5 "\n\tv_mov_b32 %6, v" #N6 "\n\tv_mov_b32 %7, v" #N7 \
+               "\n\tv_mov_b32 %8, v" #N8 "\n\tv_mov_b32 %9, v" #N9 "\n\tv_mov_b32 %10, v" #N10                      \
+               "\n\tv_mov_b32 %11, v" #N11 "\n\tv_mov_b32 %12, v" #N12 "\n\tv_mov_b32 %13, v" #N13                  \
+               "\n\tv_mov_b32 %14, v" #N14 "\n\tv_mov_b32 %15, v" #N15                                             \
+               : "=&v"(d[0]), "=&v"(d[1]), "=&v"(d[2]), "=&v"(d[3]), "=&v"(d[4]), "=&v"(d[5]), "=&v"(d[6]),           \
+                 "=&v"(d[7]), "=&v"(d[8]), "=&v"(d[9]), "=&v"(d[10]), "=&v"(d[11]), "=&v"(d[12]), "=&v"(d[13]),       \
+                 "=&v"(d[14]), "=&v"(d[15]))
+#define VITM_BODIES(OP)                                                                               \
+  switch (n) {                                                                                        \
+    case 0: OP(128, 129, 130, 131, 132, 133, 134, 135, 136, 137, 138, 139, 140, 141, 142, 143); break;\
+    case 1: OP(144, 145, 146, 147, 148, 149, 150, 151, 152, 153, 154, 155, 156, 157, 158, 159); break;\
+    case 2: OP(160, 161, 162, 163, 164, 165, 166, 167, 168, 169, 170, 171, 172, 173, 174, 175); break;\
+    case 3: OP(176, 177, 178, 179, 180, 181, 182, 183, 184, 185, 186, 187, 188, 189, 190, 191); break;\
+    case 4: OP(192, 193, 194, 195, 196, 197, 198, 199, 200, 201, 202, 203, 204, 205, 206, 207); break;\
+    case 5: OP(208, 209, 210, 211, 212, 213, 214, 215, 216, 217, 218, 219, 220, 221, 222, 223); break;\
+    case 6: OP(224, 225, 226, 227, 228, 229, 230, 231, 232, 233, 234, 235, 236, 237, 238, 239); break;\
+    default: OP(240, 241, 242, 243, 244, 245, 246, 247, 248, 249, 250, 251, 252, 253, 254, 255); break;\
+  }
+__device__ __forceinline__ void keep_words(int n, const uint32_t (&d)[16]) { VITM_BODIES(VITM_KEEP16) }
+__device__ __forceinline__ void kept_words(int n, uint32_t (&d)[16]) { VITM_BODIES(VITM_KEPT16) }
+
+// IN: VIT_LLR_I8 or VIT_LLR_HARD.
+template <int K, int BETA, int IN>
+struct DecoderM {
+  using Sh = ShapeM<K, BETA>;
+  static constexpr int P = Sh::P, S = Sh::S, BB = Sh::BB, IB = Sh::IB, NB = Sh::NB, NCLS = Sh::NCLS, NG = Sh::NG,
+                       BODY = Sh::BODY, WORDS = Sh::WORDS;
+  static constexpr bool F16 = Sh::F16;
+  static constexpr int kZero = F16 ? 0x4B400000 : 0;  // bits of metric 0 with tag 0
+  // a state that a known start cannot reach begins below every reachable one
+  static constexpr int kUnreached = -(256 * P * BETA + 1);
+
+  // per-lane constants
+  uint32_t stay[P][F16 ? (BETA + 1) / 2 : 1];  // B: +-2^P per output (bytes, or pairs of fp16): the branch that stays
+  uint32_t newest[F16 ? (BETA + 1) / 2 : 1];   // xor of that for the branch that leaves for the partner's slot (uniform)
+  uint32_t rowsign[F16 ? (BETA + 1) / 2 : 1];  // F16: bits 15 - q and 31 - q: sign of this row's LLRs at phase q
+  int tag[4];                 // own tags, per b, of the quad's register whose slot bits are 0
+  int lane;
+
+  // per-wave state
+  i32x16 o;
+  uint32_t dec[16];
+  uint32_t raw[NG][WORDS];    // LLR bytes of a body's periods: this lane's row
+  gin_t llr;                  // of the block of this lane's A row: the window's first LLR
+  int off0;                   // byte offset from there of timeline stage 0
+  int before, end;            // lowest / highest offset of a period that lies in the frame
+  int start;                  // lane tau: the timeline stage at which block tau starts, 2 t + (in state 0)
+  uint32_t *lds;
+  int body, keep;             // bodies from `keep` on are traced, and kept
+
+  __device__ __forceinline__ static uint32_t rotl_p(uint32_t x, int r) {
+    return ((x << r) | (x >> ((P - r) % P))) & (uint32_t)(S - 1);
+  }
+  __device__ __forceinline__ static int col_slot(int l) { return (l & 15) ^ (((l >> 2) & 1) ? 3 : 0); }
+  // Block of lane l's register r of the metrics, and of lane l's A row.
+  __device__ __forceinline__ static int tau_of(int l, int r) {
+    return ((((r >> 2) >> BB) << 4) | ((l >> 4) << 2) | (r & 3)) >> IB;
+  }
+  __device__ __forceinline__ static int tau_a(int l) { return ((((l >> 4) >> BB) << 4) | (l & 15)) >> IB; }
+  // Register's share of the slot index.
+  static constexpr int reg_slot(int r) { return (((r >> 2) & ((1 << BB) - 1)) << 4) | ((r & ((1 << IB) - 1)) << 6); }
+
+  // Parity pattern (bit b) of slot bits st in the branch that stays, phase q.
+  __device__ __forceinline__ static uint32_t pattern(const uint32_t *gen, int q, uint32_t st) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int b = 0; b < BETA; ++b) {
+      const uint32_t m = rotl_p(gen[b] & (uint32_t)(S - 1), q) ^ (((gen[b] >> P) & 1u) << q);
+      c |= (uint32_t)(__builtin_popcount(m & st) & 1) << b;
+    }
+    return c;
+  }
+  // Word w of a stage's B operand for sign pattern c.
+  __device__ __forceinline__ static uint32_t signs(uint32_t c, int w) {
+    uint32_t v = 0;
+    if constexpr (F16) {
+      constexpr uint32_t one = (uint32_t)(15 + P) << 10;  // fp16 2^P
+#pragma unroll
+      for (int b = 2 * w; b < BETA && b < 2 * w + 2; ++b)
+        v |= (one | (((c >> b) & 1) ? 0x8000u : 0u)) << (16 * (b - 2 * w));
+    } else {
+#pragma unroll
+      for (int b = 0; b < BETA; ++b) v |= (((c >> b) & 1) ? 0x100u - S : (uint32_t)S) << (8 * b);
+    }
+    return v;
+  }
+
+  __device__ __forceinline__ void setup(const uint32_t *gen) {
+    lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    constexpr int W = F16 ? (BETA + 1) / 2 : 1;
+    uint32_t top = 0;
+#pragma unroll
+    for (int b = 0; b < BETA; ++b) top |= ((gen[b] >> P) & 1u) << b;
+    const uint32_t st = (uint32_t)(col_slot(lane) | (((lane >> 4) & ((1 << BB) - 1)) << 4));
+    const uint32_t row = (uint32_t)(lane & ((1 << IB) - 1)) << 6;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      newest[w] = signs(0, w) ^ signs(top, w);
+      rowsign[w] = 0;
+    }
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+      const uint32_t c = pattern(gen, q, st);
+#pragma unroll
+      for (int w = 0; w < W; ++w) stay[q][w] = signs(c, w);
+      if constexpr (F16) {
+        const uint32_t s = pattern(gen, q, row);
+#pragma unroll
+        for (int w = 0; w < W; ++w) rowsign[w] |= (((s >> (2 * w)) & 1) << (15 - q)) | (((s >> (2 * w + 1)) & 1) << (31 - q));
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) tag[b] = (S - 1) ^ (col_slot(lane) | reg_slot(4 * b));
+  }
+  __device__ __forceinline__ int own_tag(int r) const { return tag[r >> 2] - (reg_slot(r) & ~63); }
+
+  // ---- LLRs: period g of body bd, this lane's row.
+  // Hard decisions become +-1 when the period's first stage runs (not at the
+  // load, which would wait for it).
+  template <int G>
+  __device__ __forceinline__ void to_pm1() {
+    if constexpr (IN == VIT_LLR_HARD) {
+#pragma unroll
+      for (int i = 0; i < WORDS; ++i) raw[G][i] = hard_to_pm1(raw[G][i]);
+    }
+  }
+  // (offset inside the frame, or past the window's last period: then clamped)
+  template <int G>
+  __device__ __forceinline__ void load_period(int bd) {
+    int at = off0 + (bd * BODY + G * P) * BETA;
+    at = at < end ? at : end;
+    const gin_t p = llr + at;
+#pragma unroll
+    for (int i = 0; i < Sh::FULL; ++i) raw[G][i] = ((gword_t)p)[i];
+    if constexpr (Sh::REM) raw[G][Sh::FULL] = *(gword_t)(p + Sh::BYTES - 4);
+  }
+  // Same where the period may begin before the frame: dword by dword, a dword
+  // that straddles the frame's first byte read from that byte on.
+  template <int G>
+  __device__ __forceinline__ void load_period_checked(int bd) {
+    int at = off0 + (bd * BODY + G * P) * BETA;
+    at = at < end ? at : end;
+#pragma unroll
+    for (int i = 0; i < WORDS; ++i) {
+      const int a = i < Sh::FULL ? at + 4 * i : at + Sh::BYTES - 4;
+      const int c = a > before ? a : before;
+      raw[G][i] = *(gword_t)(llr + c) << ((8 * (c - a)) & 31);
+    }
+  }
+
+  // LLR bytes of the period's stage j in the low BETA bytes.
+  template <int G, int J>
+  __device__ __forceinline__ uint32_t stage_bytes() const {
+    constexpr int i = J * BETA / 4, bs = J * BETA % 4;
+    // (a last partial dword holds the period's last four bytes)
+    if constexpr (Sh::REM && J == P - 1) return raw[G][Sh::FULL] >> (8 * (4 - BETA));
+    else if constexpr (bs == 0) return raw[G][i];
+    else if constexpr (bs + BETA <= 4) return raw[G][i] >> (8 * bs);
+    else return __builtin_amdgcn_alignbyte(raw[G][i + 1 < WORDS ? i + 1 : i], raw[G][i], bs);
+  }
+
+  // fp16 values of a stage's LLR bytes, exact: 0x6400 | (byte + 128) is 1152
+  // more than the byte; the row's signs on top.
+  template <int Q>
+  __device__ __forceinline__ f16x4 stage_f16(uint32_t w) const {
+    uint32_t a[2] = {0, 0};
+    int q = Q;
+    asm volatile("" : "+s"(q));
+    const uint32_t h = __builtin_amdgcn_perm(0u, w, 0x0C010C00u) ^ 0x64806480u;
+    const f16x2 lo = __builtin_bit_cast(f16x2, h) - (f16x2){(_Float16)1152.0f, (_Float16)1152.0f};
+    a[0] = __builtin_bit_cast(uint32_t, lo) ^ ((rowsign[0] << q) & 0x80008000u);
+    if constexpr (BETA > 2) {
+      constexpr uint32_t sel = BETA > 3 ? 0x0C030C02u : 0x0C0C0C02u, off = BETA > 3 ? 0x64806480u : 0x00006480u;
+      const uint32_t g = __builtin_amdgcn_perm(0u, w, sel) ^ off;
+      const f16x2 hi = __builtin_bit_cast(f16x2, g) - (f16x2){(_Float16)1152.0f, (_Float16)(BETA > 3 ? 1152.0f : 0.0f)};
+      a[1] = __builtin_bit_cast(uint32_t, hi) ^ ((rowsign[F16 && BETA > 2 ? 1 : 0] << q) & 0x80008000u);
+    }
+    return pair(a[0], a[1]);
+  }
+  __device__ __forceinline__ static f16x4 pair(uint32_t lo, uint32_t hi) {
+    return __builtin_bit_cast(f16x4, ((uint64_t)hi << 32) | lo);
+  }
+
+  template <int Q>
+  __device__ __forceinline__ static int exchange(int v) {
+    return devi::exchange<Q>(v);
+  }
+
+  // Blocks that start at timeline stage t: their start metrics.  (Rare: kept
+  // out of loop-invariant code motion, which would hold its values in
+  // registers through every body.)
+  __device__ __forceinline__ void set_starts(int t) {
+    int packed = start, from = lane;
+    asm volatile("" : "+v"(packed), "+v"(from));
+#pragma unroll
+    for (int c = 0; c < NCLS; ++c) {
+      // registers of class c hold block tau_of(lane, r) for any r of the class
+      const int rep = IB == 2 ? 0 : IB == 1 ? 2 * c : ((c >> 2) << (2 + BB)) | (c & 3);
+      const int st = __builtin_amdgcn_ds_bpermute(tau_of(from, rep) << 2, packed);
+      const bool now = (st >> 1) == t;
+      const int far = (st & 1) ? kUnreached * S : 0;          // slots other than 0
+      const int far0 = (from & 15) ? far : 0;                 // registers whose share of the slot is 0
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int cls = ((((r >> 2) >> BB) << 2) | (r & 3)) >> IB;
+        if (cls != c) continue;
+        o[r] = now ? kZero + own_tag(r) + (reg_slot(r) ? far : far0) : o[r];
+      }
+    }
+  }
+
+  // One trellis stage at body offset G.
+  template <int G, bool GUARD>
+  __device__ __forceinline__ void step() {
+    constexpr int q = G % P, g = G / P;
+    if constexpr (GUARD) {
+      const int t = body * BODY + G;
+      if (__builtin_amdgcn_ballot_w64((start >> 1) == t)) set_starts(t);
+    }
+    if constexpr (q == 0) to_pm1<g>();
+    const uint32_t w = stage_bytes<g, q>();
+    uint32_t flip[F16 && BETA > 2 ? 2 : 1];
+#pragma unroll
+    for (uint32_t x = 0; x < sizeof(flip) / 4; ++x) {
+      flip[x] = newest[x];
+      asm volatile("" : "+s"(flip[x]));  // (keeps the products out of loop-invariant code motion)
+    }
+    i32x16 out;
+    __builtin_amdgcn_s_setprio(1);
+    if constexpr (F16) {
+      const f16x4 a = stage_f16<q>(w);
+      const f32x16 c = __builtin_bit_cast(f32x16, o);
+      constexpr int h = BETA > 2 ? 1 : 0;
+      const f16x4 leave = pair(stay[q][0] ^ flip[0], h ? stay[q][h] ^ flip[h] : 0u);
+      out = __builtin_bit_cast(i32x16, __builtin_amdgcn_mfma_f32_16x16x4f16(a, leave, c, 0, 0, 0));
+      o = __builtin_bit_cast(i32x16, __builtin_amdgcn_mfma_f32_16x16x4f16(a, pair(stay[q][0], h ? stay[q][h] : 0u), c,
+                                                                          0, 0, 0));
+    } else {
+      out = __builtin_amdgcn_mfma_i32_16x16x4i8((int)w, (int)(stay[q][0] ^ flip[0]), o, 0, 0, 0);
+      o = __builtin_amdgcn_mfma_i32_16x16x4i8((int)w, (int)stay[q][0], o, 0, 0, 0);
+    }
+    __builtin_amdgcn_s_setprio(0);
+    if constexpr (q == P - 1) {  // the period's LLRs are used up
+      constexpr int next = (g + Sh::LOOK) % NG, later = (g + Sh::LOOK) / NG;
+      if constexpr (GUARD) load_period_checked<next>(body + later);
+      else load_period<next>(body + later);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      if constexpr (q < 4) o[r] = max_i(o[r], exchange<(q < 4 ? q : 0)>(out[r]));
+      else o[r] = max_i(o[r], out[r ^ (q < 6 ? 4 << (q < 4 ? 0 : q - 4) : 1 << (q < 6 ? 0 : q - 6))]);
+    }
+    if constexpr (q == P - 1) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        dec[r] = __builtin_amdgcn_alignbit((uint32_t)o[r], dec[r], P);
+        o[r] = ((o[r] & -S) | tag[r >> 2]) - (reg_slot(r) & ~63);
+      }
+    }
+    if constexpr (F16 && (G + 1) % Sh::RENORM == 0) {
+      // less the metric of slot 0 (state 0, always reachable): lane 0 of the
+      // row, register i of b = 0
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int ref = o[i & ~((1 << IB) - 1)];
+        const int d = (__builtin_amdgcn_update_dpp(0, ref, 0x150, 0xF, 0xF, true) & -S) - kZero;  // row_newbcast:0
+#pragma unroll
+        for (int b = 3; b >= 0; --b) {
+          if ((i & ((1 << IB) - 1)) != 0 || b != 0) o[4 * b + i] -= d;
+        }
+        if (((i + 1) & ((1 << IB) - 1)) == 0) o[i & ~((1 << IB) - 1)] -= d;  // the reference last
+      }
+    }
+    if constexpr (G == BODY - 1) {
+      const int at = body - keep;
+      if (at >= Sh::NR) {
+        store_words(at - Sh::NR, dec);
+      } else {
+        keep_words(at, dec);
+      }
+    }
+  }
+
+  // A body's survivor words to LDS: [slot's complement][tau], the quad's
+  // registers together.
+  __device__ __forceinline__ void store_words(int region, const uint32_t (&d)[16]) {
+    const int pos = ((15 - col_slot(lane)) << 4) | ((lane >> 4) << 2);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      // b's slot bits complemented, its block bits as they are
+      constexpr int sb = (1 << BB) - 1;
+      const int row = (b & ~sb) | (sb - (b & sb));
+      u32x4 v;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i ^ ((1 << IB) - 1)] = d[4 * b + i];
+      *(u32x4 *)(lds + region * 1024 + row * 256 + pos) = v;
+    }
+  }
+  // Where block tau's decoded word of body n goes: over the survivors of a
+  // region that has been traced (the register bodies use region 0 in turn, so
+  // they and body NR leave theirs in region 1).
+  __device__ __forceinline__ static int decoded_at(int n) {
+    return n > Sh::NR ? (n - Sh::NR) * 1024 : 1024 + 128 + (Sh::NR - n) * 64;
+  }
+  static_assert(128 + (Sh::NR + 1) * 64 <= 1024, "decoded words of the register bodies");
+
+  // Dword within a body's survivors of block tau's word for complement uc.
+  __device__ __forceinline__ static int word_at(uint32_t uc, int tau) {
+    int at = ((tau >> 4) << (8 + BB)) + (int)((uc & ((16u << BB) - 1u)) << 4) + ((tau & 15) << IB);
+    if constexpr (IB) at += (int)(uc >> (4 + BB));
+    return at;
+  }
+};
+
+#define VITM_G1(NN, M)                                     \
+  if constexpr ((NN) < (M)) {                              \
+    if ((NN) >= from) D.template step<(NN), true>();          \
+  }
+#define VITM_U1(NN, M) \
+  if constexpr ((NN) < (M)) D.template step<(NN), false>();
+#define VITM_X8(X, B, M)                                                                 \
+  X(B + 0, M) X(B + 1, M) X(B + 2, M) X(B + 3, M) X(B + 4, M) X(B + 5, M) X(B + 6, M)   \
+  X(B + 7, M)
+#define VITM_X32(X, M) VITM_X8(X, 0, M) VITM_X8(X, 8, M) VITM_X8(X, 16, M) VITM_X8(X, 24, M)
+
+__device__ __forceinline__ int wave_max_all(int v) { return __builtin_amdgcn_readfirstlane(devi::wave_max(v)); }
+
+__device__ __forceinline__ void lds_phase() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Periods that the entry offset r skips are the second body's.  (With a
+// shorter look-ahead the last ones are loaded again in the course.)
+template <int G, class D>
+__device__ __forceinline__ void first_loads(D &d, int r) {
+  if constexpr (G < D::NG) {
+    d.template load_period_checked<G>((G + 1) * D::P <= r ? 1 : 0);
+    if (G == r / D::P && r % D::P != 0) d.template to_pm1<G>();  // entered past its first stage
+    first_loads<G + 1>(d, r);
+  }
+}
+
+// Decode NB blocks; lane tau < NB describes block tau (lanes above: any block
+// again).  The caller guarantees windows of at least P stages that lie in
+// memory from `before` bytes ahead on.
+// `describe` is called before the recursion and again after it, which costs
+// less than holding its result in registers.
+template <int K, int BETA, int IN, class Describe>
+__device__ __forceinline__ void decode_tile(DecoderM<K, BETA, IN> &D, Describe describe) {
+  Blk bk = describe();
+  using Sh = ShapeM<K, BETA>;
+  constexpr int P = Sh::P, S = Sh::S, NB = Sh::NB, NCLS = Sh::NCLS, NG = Sh::NG, BODY = Sh::BODY;
+  const int lane = D.lane;
+  const int most = wave_max_all(bk.M);
+  const int r = (BODY - most % BODY) % BODY;
+  const int nbody = (most + r) / BODY;
+  const int begin = nbody * BODY - bk.M;
+  D.start = 2 * begin + (bk.known ? 1 : 0);
+  const int last_start = wave_max_all(begin);
+  const int grp_lo = -wave_max_all(-(begin + bk.core)) / BODY;  // the first body with a core bit's decision
+  D.keep = grp_lo;
+  {
+    const int from = D.tau_a(lane) << 2;
+    const uint64_t p = (uint64_t)bk.llr;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)p);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(p >> 32));
+    D.llr = (gin_t)(((uint64_t)hi << 32) | lo);
+    const int M = __builtin_amdgcn_ds_bpermute(from, bk.M);
+    D.off0 = (M - nbody * BODY) * BETA;
+    D.before = -__builtin_amdgcn_ds_bpermute(from, bk.before);
+    D.end = (M - P) * BETA;
+  }
+#pragma unroll
+  for (int x = 0; x < 16; ++x) {
+    D.o[x] = D.kZero + D.own_tag(x);
+    D.dec[x] = 0u;
+  }
+  first_loads<0>(D, r);
+  for (D.body = 0; D.body < nbody && D.body * BODY <= last_start; ++D.body) {
+    const int from = D.body == 0 ? r : 0;
+    VITM_X32(VITM_G1, BODY)
+  }
+  for (; D.body < nbody; ++D.body) {
+    VITM_X32(VITM_U1, BODY)
+  }
+  lds_phase();
+  bk = describe();
+  const int gcore = nbody * BODY - bk.M + bk.core;
+
+  // ---- traceback starts: block tau's best state (largest metric, largest
+  // complement) to lane tau
+  uint32_t uc = S - 1;
+#pragma unroll
+  for (int c = 0; c < NCLS; ++c) {
+    int m = INT32_MIN;
+#pragma unroll
+    for (int x = 0; x < 16; ++x) {
+      // class of register x: the part of tau that the register gives
+      const int cls = (((((x >> 2) >> Sh::BB) << 2) | (x & 3)) >> Sh::IB);
+      if (cls == c) m = max_i(m, D.o[x]);
+    }
+    m = max_i(m, devi::exchange<0>(m));
+    m = max_i(m, devi::exchange<1>(m));
+    m = max_i(m, devi::exchange<2>(m));
+    m = max_i(m, devi::exchange<3>(m));
+    // tau = (class's b part, row quad, class's register part)
+    constexpr int kQ = 2 - Sh::IB;  // bits of tau below the row quad
+    const int got = __builtin_amdgcn_ds_bpermute((((lane >> kQ) & 3) << 4) << 2, m);
+    const int mine = ((lane >> (kQ + 2)) << kQ) | (lane & ((1 << kQ) - 1));
+    uc = mine == c ? (uint32_t)got & (uint32_t)(S - 1) : uc;
+  }
+  if (bk.zero) uc = S - 1;
+  const uint32_t lam_start = uc ^ (uint32_t)(S - 1);
+  for (int grp = nbody - 1 - grp_lo; grp >= 0; --grp) {
+    int region = grp - Sh::NR;
+    if (region < 0) {
+      region = 0;
+      uint32_t d[16];
+      kept_words(grp, d);
+      D.store_words(0, d);
+      lds_phase();
+    }
+    if (lane < NB) {
+      const uint32_t *w = D.lds + region * 1024;
+      uint32_t acc = 0;
+#pragma unroll
+      for (int g = NG - 1; g >= 0; --g) {
+        uc = (w[D.word_at(uc, lane)] >> (32 - BODY + g * P)) & (uint32_t)(S - 1);
+        acc |= uc << (g * P);
+      }
+      D.lds[D.decoded_at(grp) + lane] = ~acc;
+    }
+    lds_phase();
+  }
+  if (lane < NB) D.lds[1024 + 64 + lane] = lam_start;  // (region 1 has been traced)
+  lds_phase();
+  lds_phase();
+
+  // ---- output: 64 / NB lanes per block, a dword each where it is whole
+  {
+    constexpr int LPT = 64 / NB;
+    const int tau = lane / LPT, from = tau << 2;
+    const int gc = __builtin_amdgcn_ds_bpermute(from, gcore) + P - grp_lo * BODY;
+    const int emit = __builtin_amdgcn_ds_bpermute(from, (int)bk.emit);
+    const int ncore = emit ? __builtin_amdgcn_ds_bpermute(from, bk.ncore) : 0;
+    const uint64_t p = (uint64_t)bk.out;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)p);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(p >> 32));
+    const gout_t out = (gout_t)(((uint64_t)hi << 32) | lo);
+    constexpr uint32_t body_mask = BODY == 32 ? 0xffffffffu : ((1u << (BODY % 32)) - 1u);
+    for (int bit = (lane % LPT) * 32; bit < ncore; bit += 32 * LPT) {
+      const int at = gc + bit;
+      const int wa = at / BODY, sh = at - wa * BODY;
+      auto word = [&](int i) -> uint64_t {
+        if (i < nbody - grp_lo) return D.lds[D.decoded_at(i) + tau] & body_mask;
+        return i == nbody - grp_lo ? D.lds[1024 + 64 + tau] : 0u;
+      };
+      uint64_t cat = word(wa) | (word(wa + 1) << BODY);
+      if constexpr (BODY < 32) cat |= word(wa + 2) << (2 * BODY);
+      uint32_t v = (uint32_t)(cat >> sh);
+      const int left = ncore - bit;
+      if (left >= 32) {
+        *(__attribute__((address_space(1))) una32 *)(out + (bit >> 3)) = v;
+      } else {
+        v &= (1u << left) - 1u;
+        for (int j = 0; j < left; j += 8) out[(bit + j) >> 3] = (uint8_t)(v >> j);
+      }
+    }
+  }
+  lds_phase();
+}
+
+// Stream kernel: wave w decodes blocks [NB w, NB w + NB), then those NB x
+// (waves of the grid) further on; blocks past the last are the last again, not
+// written.
+template <int K, int BETA, int IN>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8), amdgpu_num_vgpr(64))) void vit_blocked_mx_kernel(DecodeArgs a) {
+  using Sh = ShapeM<K, BETA>;
+  extern __shared__ uint32_t vit_ldsm[];
+  asm volatile("" ::: "v255");
+  DecoderM<K, BETA, IN> D;
+  D.setup(a.gen);
+  D.lds = vit_ldsm;
+  const int64_t tiles = (a.nblocks + Sh::NB - 1) / Sh::NB;
+  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    decode_tile(D, [&] {
+      int tau = D.lane & (Sh::NB - 1);
+      asm volatile("" : "+v"(tau));  // (computed anew at each call)
+      const int64_t want = tile * Sh::NB + tau;
+      const int64_t blk = want < a.nblocks ? want : a.nblocks - 1;
+      const int64_t cs = blk * a.L;
+      const int64_t ce = (cs + a.L < a.n) ? cs + a.L : a.n;
+      const int64_t s = (cs - a.v1 > 0) ? cs - a.v1 : 0;
+      const int64_t e = (ce + a.v2 < a.N) ? ce + a.v2 : a.N;
+      Blk b;
+      b.llr = (const uint8_t *)a.llr + s * BETA;
+      b.out = a.out + (cs >> 3);
+      b.before = (int)(s < (1 << 18) ? s * BETA : 1 << 20);
+      b.M = (int)(e - s);
+      b.core = (int)(cs - s);
+      b.ncore = (int)(ce - cs);
+      b.known = s == 0;
+      b.zero = a.terminated && e == a.N;
+      b.emit = want < a.nblocks;
+      return b;
+    });
+  }
+}
+
+// Batch kernel: the code's items (longest first), NB at a time.
+template <int K, int BETA, int IN>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8), amdgpu_num_vgpr(64))) void vit_batch_mx_kernel(BatchArgs a) {
+  using Sh = ShapeM<K, BETA>;
+  extern __shared__ uint32_t vit_ldsm[];
+  asm volatile("" ::: "v255");
+  const int nitems = __builtin_amdgcn_readfirstlane(a.header[kMaxCodes + a.code_index]);
+  const int tiles = (nitems + Sh::NB - 1) / Sh::NB;
+  if ((int)blockIdx.x >= tiles) return;
+  DecoderM<K, BETA, IN> D;
+  D.setup(a.gen);
+  D.lds = vit_ldsm;
+  const WorkItem *items = a.items + a.header[2 * kMaxCodes + a.code_index];
+  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    decode_tile(D, [&] {
+      int tau = D.lane & (Sh::NB - 1);
+      asm volatile("" : "+v"(tau));  // (loaded anew at each call)
+      const int want = tile * Sh::NB + tau;
+      const WorkItem it = items[want < nitems ? want : nitems - 1];
+      Blk b;
+      b.llr = (const uint8_t *)a.llr + it.llr_off + (int64_t)it.s * BETA;
+      b.out = a.out + it.out_off + (it.cs >> 3);
+      b.before = it.s < (1 << 18) ? it.s * BETA : 1 << 20;
+      b.M = it.e - it.s;
+      b.core = it.cs - it.s;
+      b.ncore = it.ce - it.cs;
+      b.known = (it.flags & 1) != 0;
+      b.zero = (it.flags & 2) != 0;
+      b.emit = want < nitems;
+      return b;
+    });
+  }
+}
+
+#undef VITM_G1
+#undef VITM_U1
+#undef VITM_X8
+#undef VITM_X32
+
+}  // namespace devm
+
+// Kernel instances for (K, beta, input kind VIT_LLR_I8 / VIT_LLR_HARD), taking
+// DecodeArgs, or BatchArgs.
+template <int K>
+void *pick_kernel_mx_k(int beta, int in, bool batch) {
+  auto pick = [&](auto bt) -> void * {
+    constexpr int B = decltype(bt)::value;
+    if (batch)
+      return in == VIT_LLR_HARD ? (void *)devm::vit_batch_mx_kernel<K, B, VIT_LLR_HARD>
+                                : (void *)devm::vit_batch_mx_kernel<K, B, VIT_LLR_I8>;
+    return in == VIT_LLR_HARD ? (void *)devm::vit_blocked_mx_kernel<K, B, VIT_LLR_HARD>
+                              : (void *)devm::vit_blocked_mx_kernel<K, B, VIT_LLR_I8>;
+  };
+  switch (beta) {
+    case 2: return pick(std::integral_constant<int, 2>{});
+    case 3: return pick(std::integral_constant<int, 3>{});
+    case 4: return pick(std::integral_constant<int, 4>{});
+  }
+  return nullptr;
+}
+
+void *pick_kernel_mx_k5(int beta, int in, bool batch);
+void *pick_kernel_mx_k6(int beta, int in, bool batch);
+void *pick_kernel_mx_k7(int beta, int in, bool batch);
+void *pick_kernel_mx_k8(int beta, int in, bool batch);
+void *pick_kernel_mx_k9(int beta, int in, bool batch);
+
+}  // namespace vit

@@ -108,13 +108,26 @@ struct BatchLaunch {
   int lds_words_per_wave;
   int items_per_wave;        // work items a wave takes at once (2 for the 16-bit metric kernels)
   int metric_bits;           // 16 or 32 for integer inputs, 0 for FP32
+  int k, num_cu, max_lds;    // the code, and the device it was planned on
+  const void *mx_fn;         // matrix-core kernel for the same blocks, or nullptr
+  size_t mx_lds;             // its dynamic LDS bytes
 };
 // Fill *bl for a code (k, beta, generators, input kind, metric choice as
 // DecodeArgs::metric_bits) decoding blocks of at most max_block_stages
-// stages with `wpb` waves per workgroup.  Returns hipSuccess; sets
-// *unsupported when the shape is not available.
+// stages with `wpb` waves per workgroup.  traced: most stages from a block's
+// first core bit to its end, 0 to leave the matrix-core kernels out.  Returns
+// hipSuccess; sets *unsupported when the shape is not available.
 hipError_t plan_batch_launch(int k, int beta, const uint32_t *gen, int in, int metric_bits, int64_t max_block_stages,
-                             int wpb, BatchLaunch *bl, int *unsupported, const char **why);
+                             int64_t traced, int wpb, BatchLaunch *bl, int *unsupported, const char **why);
+// The kernel and grid for `count` work items: the matrix-core kernel where it
+// is the faster one.  whole_words: every frame holds at least 4 bytes of LLRs
+// (that kernel reads them by dwords).
+struct BatchGrid {
+  const void *fn;
+  unsigned grid, block;
+  size_t lds;
+};
+BatchGrid batch_grid_for(const BatchLaunch &bl, int64_t count, int64_t max_block_stages, bool whole_words);
 // Workgroups of one batch kernel launch over `count` work items (the grid rule
 // of vit_shapes.h applied to the waves' units of work).
 unsigned batch_launch_grid(const BatchLaunch &bl, int64_t count, int64_t max_block_stages, int num_cu);

@@ -1,0 +1,6 @@
+// vit_kernels_mx_k9.hip -- matrix-core integer kernel instances (stream and batch) for constraint length k = 9.
+#include "vit_decoder_mx.h"
+
+namespace vit {
+void *pick_kernel_mx_k9(int beta, int in, bool batch) { return pick_kernel_mx_k<9>(beta, in, batch); }
+}  // namespace vit

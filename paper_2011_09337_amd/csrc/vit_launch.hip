@@ -3,6 +3,7 @@
 #include "vit_decoder.h"
 #include "vit_decoder16.h"
 #include "vit_decoder_int.h"
+#include "vit_decoder_mx.h"
 #include "vit_shapes.h"
 
 namespace vit {
@@ -33,6 +34,17 @@ void *pick_kernel_int(int k, int beta, const uint32_t *gen, int in, bool batch) 
     case 7: return pick_kernel_int_k7(beta, top, in, batch);
     case 8: return pick_kernel_int_k8(beta, top, in, batch);
     case 9: return pick_kernel_int_k9(beta, top, in, batch);
+  }
+  return nullptr;
+}
+
+void *pick_kernel_mx(int k, int beta, int in, bool batch) {
+  switch (k) {
+    case 5: return pick_kernel_mx_k5(beta, in, batch);
+    case 6: return pick_kernel_mx_k6(beta, in, batch);
+    case 7: return pick_kernel_mx_k7(beta, in, batch);
+    case 8: return pick_kernel_mx_k8(beta, in, batch);
+    case 9: return pick_kernel_mx_k9(beta, in, batch);
   }
   return nullptr;
 }
@@ -178,6 +190,75 @@ hipError_t launch_blocked16(const DecodeArgs &a, hipStream_t stream, int *unsupp
   return hipGetLastError();
 }
 
+// ---- the matrix-core kernels (vit_decoder_mx.h)
+
+int mx_blocks(int k) { return k <= 5 ? 64 : 1 << (11 - k); }  // per wave
+
+// Survivor regions of a wave whose blocks are traced over `traced` stages (from
+// the first core bit to the window's end) beyond those in registers.
+int64_t mx_lds_bytes(int k, int64_t traced) {
+  const int64_t body = body_len(k);
+  const int64_t regions = (traced + body - 1) / body - devm::kKept;
+  return (regions > 2 ? regions : 2) * 4096;
+}
+
+// Waves a CU holds: two per SIMD by registers, fewer by LDS (in units of 1280 bytes).
+int mx_waves_per_cu(int64_t lds, int max_lds) {
+  const int64_t unit = (lds + 1279) / 1280 * 1280;
+  const int64_t by_lds = max_lds / unit;
+  return (int)(by_lds < 8 ? by_lds : 8);
+}
+
+// Which integer kernel decodes `blocks` blocks sooner, by the time each takes
+// per stage (nanoseconds, measured with the chip full and with one wave on a
+// SIMD; the stages of a block are the same for both).  The one-block kernel
+// takes 11.3 per block, 64 states and SIMD where the chip is full (2^24 bits
+// of K=7, L = 256: 210 us) and at least 24 / 30 / 70 (k <= 7, 8, 9; one wave's
+// latency).  A wave of the matrix-core kernel takes 92 / 100 / 115 alone on a
+// SIMD and half as long again beside a second one, for 64..4 blocks, but only
+// as many as LDS holds survivors for run at once.  Measured on both sides of
+// the line: K=7, L = 256, 4096 blocks 20 us by the one-block kernel and 34 by
+// this one, 16384 blocks 61 and 37, 65536 blocks 210 and 91; K=7, L = 512
+// (four waves a CU), 8192 blocks 60 and 59, 32768 blocks 198 and 118; K=7,
+// L = 1024 (one wave a CU), 16384 blocks 218 and 400; K=9, L = 256, 1024 blocks
+// 27 and 40, 4096 blocks 67 and 43, 16384 blocks 236 and 104.
+bool mx_is_faster(int k, int64_t blocks, int64_t lds, int num_cu, int max_lds) {
+  const int per_cu = mx_waves_per_cu(lds, max_lds);
+  if (per_cu < 1) return false;
+  const int64_t simds = 4 * (int64_t)num_cu, slots = (int64_t)per_cu * num_cu;
+  const int64_t tiles = (blocks + mx_blocks(k) - 1) / mx_blocks(k);
+  const double regs = k > 7 ? 1 << (k - 7) : 1;
+  const double latency = k <= 7 ? 24.0 : k == 8 ? 30.0 : 70.0;
+  const double full = 11.3 * regs * (double)blocks / (double)simds;
+  const double one_block = full > latency ? full : latency;
+  const double wave = (k <= 7 ? 92.0 : k == 8 ? 100.0 : 115.0) * ((tiles < slots ? tiles : slots) > simds ? 1.55 : 1.0);
+  return (double)((tiles + slots - 1) / slots) * wave < one_block;
+}
+
+// Workgroups (of one wave): one per tile, refilled by the dispatcher, where
+// two waves share a SIMD; where LDS allows at most one per SIMD, that many
+// persistent waves (K=7, L = 512, 2^24 bits: 117 us against 149, the
+// dispatcher's refills landing two on one SIMD).
+unsigned mx_grid(int k, int64_t blocks, int64_t lds, int num_cu, int max_lds) {
+  const int64_t tiles = (blocks + mx_blocks(k) - 1) / mx_blocks(k);
+  const int per_cu = mx_waves_per_cu(lds, max_lds);
+  const int64_t slots = (int64_t)per_cu * num_cu;
+  return (unsigned)(per_cu <= 4 && tiles > slots ? slots : tiles);
+}
+
+hipError_t launch_blocked_mx(const DecodeArgs &a, int64_t lds, hipStream_t stream) {
+  void *fn = pick_kernel_mx(a.k, a.beta, a.llr_type, false);
+  if (lds > 65536) {
+    const hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (err != hipSuccess) return err;
+  }
+  DecodeArgs args = a;
+  void *kargs[] = {&args};
+  const hipError_t err = hipLaunchKernel(fn, dim3(mx_grid(a.k, a.nblocks, lds, t_dev.num_cu, t_dev.max_lds)), dim3(64), kargs, (size_t)lds, stream);
+  if (err != hipSuccess) return err;
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsupported, const char **why) {
@@ -193,6 +274,10 @@ hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsuppor
       return hipSuccess;
     }
     if (m == kMetric16) return launch_blocked16(a, stream, unsupported, why);
+    if (a.k >= 5 && a.nblocks > 1) {
+      const int64_t lds = mx_lds_bytes(a.k, a.L + a.v2);
+      if (lds <= t_dev.max_lds && mx_is_faster(a.k, a.nblocks, lds, t_dev.num_cu, t_dev.max_lds)) return launch_blocked_mx(a, lds, stream);
+    }
   } else if (a.llr_type != VIT_LLR_F32) {
     // subframe traceback: the exact-in-fp32 integer kernels only
     if (a.metric_bits == kMetric16) {
@@ -270,13 +355,25 @@ unsigned batch_launch_grid(const BatchLaunch &bl, int64_t count, int64_t max_blo
   return batch_grid(units, (int)(bl.block / 64), max_block_stages, bl.grid, num_cu);
 }
 
+BatchGrid batch_grid_for(const BatchLaunch &bl, int64_t count, int64_t max_block_stages, bool whole_words) {
+  const int64_t lds = (int64_t)bl.mx_lds;
+  if (bl.mx_fn && whole_words && mx_is_faster(bl.k, count, lds, bl.num_cu, bl.max_lds))
+    return {bl.mx_fn, mx_grid(bl.k, count, lds, bl.num_cu, bl.max_lds), 64, bl.mx_lds};
+  return {bl.fn, batch_launch_grid(bl, count, max_block_stages, bl.num_cu), bl.block, bl.lds};
+}
+
 hipError_t plan_batch_launch(int k, int beta, const uint32_t *gen, int in, int metric_bits, int64_t max_block_stages,
-                             int wpb, BatchLaunch *bl, int *unsupported, const char **why) {
+                             int64_t traced, int wpb, BatchLaunch *bl, int *unsupported, const char **why) {
   *unsupported = 0;
   {
     const hipError_t err = device_info();
     if (err != hipSuccess) return err;
   }
+  bl->k = k;
+  bl->num_cu = t_dev.num_cu;
+  bl->max_lds = t_dev.max_lds;
+  bl->mx_fn = nullptr;
+  bl->mx_lds = 0;
   const int metric = resolve_metric(k, beta, in, metric_bits, max_block_stages, why);
   if (metric < 0) {
     *unsupported = 1;
@@ -355,6 +452,14 @@ hipError_t plan_batch_launch(int k, int beta, const uint32_t *gen, int in, int m
   bl->lds_words_per_wave = (int)(lds_wave / 4);
   bl->items_per_wave = 1;
   bl->metric_bits = metric;
+  if (in != VIT_LLR_F32 && k >= 5 && traced > 0 && mx_lds_bytes(k, traced) <= t_dev.max_lds) {
+    bl->mx_fn = pick_kernel_mx(k, beta, in, true);
+    bl->mx_lds = (size_t)mx_lds_bytes(k, traced);
+    if (bl->mx_lds > 65536) {
+      err = hipFuncSetAttribute(bl->mx_fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bl->mx_lds);
+      if (err != hipSuccess) return err;
+    }
+  }
   return hipSuccess;
 }
 

@@ -579,7 +579,7 @@ static int server_create_impl(const vit_code *codes, int32_t ncodes, const vit_t
     int unsupported = 0;
     const char *why = "";
     e = vit::plan_batch_launch(codes[c].k, codes[c].beta, codes[c].gen, cfg->llr_type, cfg->metric_bits,
-                               (int64_t)shape[c].L + shape[c].v, shape[c].waves_per_block, &s->bl[c], &unsupported,
+                               (int64_t)shape[c].L + shape[c].v, 0, shape[c].waves_per_block, &s->bl[c], &unsupported,
                                &why);
     if (e != hipSuccess) return bail(vit::api_fail_hip(e, "batch launch planning"));
     if (unsupported) return bail(api_fail(VIT_EUNSUPPORTED, "code %d: %s", c, why));
