@@ -1,48 +1,69 @@
 // vit_decoder_mx.h -- integer decoder on the matrix cores, for int8 and
 // hard-decision inputs with many blocks, on gfx950: device templates,
-// instantiated per constraint length (5 <= k <= 9) in vit_kernels_mx_k*.hip.
+// instantiated per constraint length (3 <= k <= 9) in vit_kernels_mx_k*.hip.
 //
 // The recursion is that of vit_decoder_int.h (rotating slots, metrics that
 // carry their ancestor's tag in the low P = k-1 bits, o = max(o + x, partner's
-// o - x)).  Here one wave decodes NB blocks at once (64, 32, 16, 8, 4 for
-// k = 5..9), 1024 slots in 16 registers, and both additions of a stage are
-// matrix instructions with the metrics as the accumulator:
+// o - x)).  Here one wave decodes NB blocks at once, and both additions of a
+// stage are matrix instructions with the metrics as the accumulator.  Two
+// layouts:
 //
-//   v_mfma_*_16x16x4 (4 blocks): D[b][row, col] = A_b[row, :] . B_b[:, col] + C
+//   16 registers (k = 6..9, NB = 32, 16, 8, 4: 1024 slots a wave)
+//     v_mfma_*_16x16x4 (4 blocks): D[b][row, col] = A_b[row, :] . B_b[:, col] + C
+//   4 registers ("quad", k = 3..7, NB = 64, 32, 16, 8, 4: 256 slots a wave)
+//     v_mfma_i32_4x4x4 (16 blocks)
 //
 //  * A is a stage's LLRs (the four products are the code's outputs), B the
 //    signs of each slot's branch times 2^P: one instruction adds the branch
 //    that stays in the slot, another the branch that leaves for the partner's
-//    slot, 32 matrix-pipe cycles each, and both run beside the vector work of
-//    the SIMD's other wave.  What is left for the vector unit is one max per
-//    slot and stage, and two instructions per period for the tags: 4 issue
-//    cycles per 64 slots instead of 8 and a crossbar fetch.
-//  * Slot bits 0..3 are the lanes of a row of 16 (col: lane xors 1, 2, 7, 8,
-//    which DPP reads inside the max); bits 4, 5 are the instruction's blocks b
-//    and bits 6, 7 the register within a row quad: partners in registers, no
-//    exchange at all.  The other row, quad and b indices number the blocks
-//    (tau).  A row that carries slot bits (k = 8, 9) puts their branch signs on
-//    its LLRs.
+//    slot.  What is left for the vector unit is one max per slot and stage, and
+//    two instructions per period for the tags: 4 issue cycles per 64 slots
+//    instead of 8 and a crossbar fetch.  The 16x16x4 form (32 cycles) runs beside
+//    the vector work of the SIMD's other wave; the 4x4x4 form (8 cycles, a
+//    quarter of the slots) holds the vector unit up, but a wave needs a quarter of
+//    the blocks and of the survivor space.
+//  * 16 registers: slot bits 0..3 are the lanes of a row of 16 (col: lane xors 1,
+//    2, 7, 8, which DPP reads inside the max); bits 4, 5 are the instruction's
+//    blocks b and bits 6, 7 the register within a row quad: partners in
+//    registers, no exchange at all.  The other row, quad and b indices number the
+//    blocks (tau).  A row that carries slot bits (k = 8, 9) puts their branch
+//    signs on its LLRs.
+//  * 4 registers: the lane's low P bits are the slot, its other bits and the
+//    register number the blocks.  Bits 4, 5 exchange by a permlane swap of the
+//    two candidates: the lanes of that bit hold them the other way round (their B
+//    signs are swapped), so that one swap brings both of a slot together.
+//  * All instruction blocks that belong to the same tau take their A from one of
+//    them (CBSZ, ABID), so each lane holds another dword of its row's LLRs: one
+//    load a lane brings 64 bytes of each row at k = 7 in the 4-register layout,
+//    and 16 in the other.
 //  * k <= 7: int8 LLRs straight from memory, 32-bit integer sums.  k = 8, 9
 //    need 2^P > 64, more than a byte's sign factor: fp16 operands, fp32 sums
 //    kept as 2^23 + 2^22 + integer, whose bits count like the integer's (the
 //    tags and the max work on the bits); the metrics are taken back towards 0
 //    every RENORM stages.
 //  * Blocks of different lengths share a wave: all end at the last stage of
-//    the last body; a block is set to its start metrics at its first stage.
-//  * Survivor words as in vit_decoder_int.h: those of a block's first eight
-//    traced bodies in 128 registers of their own, the others in LDS,
+//    the last body; a block is set to its start metrics at its first stage (only
+//    the bodies in which some block starts look for it: a short last block of a
+//    stream made its whole wave half as slow again when all earlier ones did).
+//  * Survivor words as in vit_decoder_int.h: those of a block's first 8 (or 16)
+//    traced bodies in 128 (or 64) registers of their own, the others in LDS,
 //    [slot][tau].  The traceback runs one lane per block, one dependent LDS read
 //    per period.
 //
-// What bounds it: a wave alone on a SIMD takes 92 ns per stage (k = 7, 16 blocks:
-// the two matrix instructions one after the other, their latency, then 16 max);
-// two waves overlap the one's matrix with the other's vector work, 140 ns for
-// both; registers and LDS hold no third.  Measured, one-block kernel / here:
-// K=7 r1/2, 2^24 int8 bits, v = 35: L = 256 210 / 91 us, L = 512 (one wave per
-// SIMD by LDS; without the register bodies two a CU and 212 us) 198 / 121;
-// K=7 r1/3, L = 256 213 / 102; K=9 r1/2, 2^22 bits, L = 256, v = 64 236 / 104;
-// K=5 r1/2, 2^24 bits, L = 256 204 / 42.
+// What bounds it.  16 registers: a wave alone on a SIMD takes 95 ns per stage
+// (k = 7, 16 blocks: the two matrix instructions one after the other, their
+// latency, then 16 max); two waves overlap the one's matrix with the other's
+// vector work, 147 ns for both; registers and LDS hold no third.  4 registers:
+// alone 44 ns per stage (4 blocks: the chain of instruction latencies), four
+// waves 92 for all: 7 ns of matrix and 14 of vector work each.  Measured, one-block
+// kernel / 16 / 4 registers, us: K=7 r1/2, 2^24 int8 bits, v = 35: L = 256
+// 210 / 84 / 113, L = 512 (LDS holds one 16-register wave a SIMD; without the
+// survivor registers two a CU and 212 us) 199 / 121 / 107; K=7 r1/2, 2^22 bits,
+// L = 512 59 / 60 / 39; K=9 r1/2, 2^22 bits, L = 256, v = 64 236 / 94 / -;
+// K=5 r1/2, 2^24 bits, L = 256 204 / - / 34 (16 registers: 48); K=3 r1/2 the
+// same 201 / - / 31.  With a row's LLRs loaded by periods in every lane (up to
+// 15 registers, unaligned) instead of by broadcast: K=7 r1/3, L = 512 123 in 16
+// registers and 242 in 4 (now 134 and 107); K=9, L = 256 104 (now 94).
 #pragma once
 
 #include "vit_decoder_int.h"
@@ -59,32 +80,40 @@ namespace devm {
 using devi::hard_to_pm1;
 using devi::max_i;
 
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kKept = 8;  // bodies whose survivors a wave keeps in registers
+// Bodies whose survivors a wave keeps in registers of its own: 128 of them in
+// the 16-register layout, 64 in the 4-register one.
+constexpr int kept_bodies(bool quad) { return quad ? 16 : 8; }
+// Dwords of a body's survivor words in LDS.
+constexpr int region_words(bool quad) { return quad ? 256 : 1024; }
 
-template <int K, int BETA>
+template <int K, int BETA, bool QUAD>
 struct ShapeM {
   static constexpr int P = K - 1;
   static constexpr int S = 1 << P;
-  static constexpr int BB = P - 4 < 2 ? P - 4 : 2;  // slot bits in b
-  static constexpr int IB = P - 4 - BB;             // slot bits in the quad's register
-  static constexpr int NB = 64 >> (BB + IB);        // blocks per wave
-  static constexpr int NCLS = NB / 4;               // blocks per lane
+  static constexpr int R = QUAD ? 4 : 16;                           // metric registers
+  static constexpr int BB = QUAD ? 0 : P - 4 < 2 ? P - 4 : 2;       // slot bits in b
+  static constexpr int IB = QUAD ? 0 : P - 4 - BB;                  // slot bits in the quad's register
+  static constexpr int NB = QUAD ? 256 >> P : 64 >> (BB + IB);      // blocks per wave
+  static constexpr int NCLS = QUAD ? 4 : NB / 4;                    // blocks per lane
   static constexpr int NG = 32 / P;                 // periods per body
   static constexpr int BODY = P * NG;
-  static constexpr int BYTES = P * BETA;            // LLR bytes of a period
-  static constexpr int FULL = BYTES / 4, REM = BYTES % 4;
-  static constexpr int WORDS = FULL + (REM ? 1 : 0);
-  static constexpr bool F16 = P > 6;
-  // Periods between an LLR load and its use (a period takes about half a
-  // microsecond), limited by registers.
-  static constexpr int LOOK = NG * WORDS <= 16 ? NG : NG < 3 ? NG : 3;
-  static constexpr int NR = kKept;  // kept bodies whose survivors stay in registers, the first of a block
+  // LLRs: a dword holds SPD stages, one load DPL dwords of every row, one per
+  // instruction block, which the instruction takes by broadcast (CBSZ, ABID).
+  static constexpr int SPD = BETA == 2 ? 2 : 1;
+  static constexpr int CBSZ = QUAD ? P - 2 : BB, DPL = 1 << CBSZ;
+  static constexpr int SPL = SPD * DPL;             // stages of a load
+  static constexpr int NL = (BODY + SPL - 1) / SPL; // loads of a body
+  static constexpr int AHEAD = !QUAD && P > 6 && NL % 4 == 0 ? 4 : NL < 16 ? NL : 16;  // loads between one and its use (registers; divides NL)
+  static constexpr bool F16 = !QUAD && P > 6;
+  static constexpr int NR = kept_bodies(QUAD);
+  static constexpr int REGION = region_words(QUAD);
   // Stages between two renormalisations of the fp32 sums, whole periods: the
   // spread 2^8 P beta + 1, and 2^7 beta a stage, stay below 2^22 / 2^P.
   static constexpr int kRoom = ((1 << 22) >> P) - 1 - 256 * P * BETA;
@@ -143,46 +172,94 @@ struct Blk {
 __device__ __forceinline__ void keep_words(int n, const uint32_t (&d)[16]) { VITM_BODIES(VITM_KEEP16) }
 __device__ __forceinline__ void kept_words(int n, uint32_t (&d)[16]) { VITM_BODIES(VITM_KEPT16) }
 
+// The same for the 4-register layout: v64..v127, compiled for 64.
+#define VITM_KEEP4(N0, N1, N2, N3)                                                                        \
+  asm volatile("v_mov_b32 v" #N0 ", %0\n\tv_mov_b32 v" #N1 ", %1\n\tv_mov_b32 v" #N2 ", %2\n\tv_mov_b32 v" #N3 ", %3" \
+               ::"v"(d[0]), "v"(d[1]), "v"(d[2]), "v"(d[3]))
+#define VITM_KEPT4(N0, N1, N2, N3)                                                                        \
+  asm volatile("v_mov_b32 %0, v" #N0 "\n\tv_mov_b32 %1, v" #N1 "\n\tv_mov_b32 %2, v" #N2 "\n\tv_mov_b32 %3, v" #N3   \
+               : "=&v"(d[0]), "=&v"(d[1]), "=&v"(d[2]), "=&v"(d[3]))
+#define VITM_BODIES4(OP)                    \
+  switch (n) {                              \
+    case 0: OP(64, 65, 66, 67); break;      \
+    case 1: OP(68, 69, 70, 71); break;      \
+    case 2: OP(72, 73, 74, 75); break;      \
+    case 3: OP(76, 77, 78, 79); break;      \
+    case 4: OP(80, 81, 82, 83); break;      \
+    case 5: OP(84, 85, 86, 87); break;      \
+    case 6: OP(88, 89, 90, 91); break;      \
+    case 7: OP(92, 93, 94, 95); break;      \
+    case 8: OP(96, 97, 98, 99); break;      \
+    case 9: OP(100, 101, 102, 103); break;  \
+    case 10: OP(104, 105, 106, 107); break; \
+    case 11: OP(108, 109, 110, 111); break; \
+    case 12: OP(112, 113, 114, 115); break; \
+    case 13: OP(116, 117, 118, 119); break; \
+    case 14: OP(120, 121, 122, 123); break; \
+    default: OP(124, 125, 126, 127); break; \
+  }
+__device__ __forceinline__ void keep_words(int n, const uint32_t (&d)[4]) { VITM_BODIES4(VITM_KEEP4) }
+__device__ __forceinline__ void kept_words(int n, uint32_t (&d)[4]) { VITM_BODIES4(VITM_KEPT4) }
+
 // IN: VIT_LLR_I8 or VIT_LLR_HARD.
-template <int K, int BETA, int IN>
+template <int K, int BETA, int IN, bool QUAD>
 struct DecoderM {
-  using Sh = ShapeM<K, BETA>;
+  using Sh = ShapeM<K, BETA, QUAD>;
   static constexpr int P = Sh::P, S = Sh::S, BB = Sh::BB, IB = Sh::IB, NB = Sh::NB, NCLS = Sh::NCLS, NG = Sh::NG,
-                       BODY = Sh::BODY, WORDS = Sh::WORDS;
+                       BODY = Sh::BODY, R = Sh::R;
   static constexpr bool F16 = Sh::F16;
   static constexpr int kZero = F16 ? 0x4B400000 : 0;  // bits of metric 0 with tag 0
   // a state that a known start cannot reach begins below every reachable one
   static constexpr int kUnreached = -(256 * P * BETA + 1);
 
   // per-lane constants
-  uint32_t stay[P][F16 ? (BETA + 1) / 2 : 1];  // B: +-2^P per output (bytes, or pairs of fp16): the branch that stays
+  uint32_t stay[P][F16 ? (BETA + 1) / 2 : 1];  // B: +-2^P per output (bytes, or pairs of fp16): the branch that stays (QUAD,
+                                               // q = 4, 5: in lanes of bit q, the one that leaves)
   uint32_t newest[F16 ? (BETA + 1) / 2 : 1];   // xor of that for the branch that leaves for the partner's slot (uniform)
-  uint32_t rowsign[F16 ? (BETA + 1) / 2 : 1];  // F16: bits 15 - q and 31 - q: sign of this row's LLRs at phase q
-  int tag[4];                 // own tags, per b, of the quad's register whose slot bits are 0
+  uint32_t rowsign[F16 ? (BETA + 1) / 2 : 1];  // F16: bits 15 - x and 31 - x: sign of this lane's LLRs in half x of the loads
+  int tag[R / 4];             // own tags, per b, of the quad's register whose slot bits are 0
   int lane;
+  uint32_t nothing;           // 0, unknown to the compiler (uniform): a copy that it must make where it stands
 
   // per-wave state
-  i32x16 o;
-  uint32_t dec[16];
-  uint32_t raw[NG][WORDS];    // LLR bytes of a body's periods: this lane's row
+  typename std::conditional<QUAD, i32x4, i32x16>::type o;
+  uint32_t dec[R];
+  uint32_t raw[Sh::AHEAD];    // the loads ahead: this lane's row and dword
+  uint32_t cur[Sh::SPD][F16 && BETA > 2 ? 2 : 1];  // the load in use, as A operands
   gin_t llr;                  // of the block of this lane's A row: the window's first LLR
-  int off0;                   // byte offset from there of timeline stage 0
-  int before, end;            // lowest / highest offset of a period that lies in the frame
+  int off0;                   // byte offset from there of this lane's dword of timeline stage 0
+  int before, end;            // lowest / highest offset of a dword that lies in the frame's window
   int start;                  // lane tau: the timeline stage at which block tau starts, 2 t + (in state 0)
   uint32_t *lds;
   int body, keep;             // bodies from `keep` on are traced, and kept
+  int decoded;                // QUAD: place of the decoded words in LDS
 
   __device__ __forceinline__ static uint32_t rotl_p(uint32_t x, int r) {
     return ((x << r) | (x >> ((P - r) % P))) & (uint32_t)(S - 1);
   }
-  __device__ __forceinline__ static int col_slot(int l) { return (l & 15) ^ (((l >> 2) & 1) ? 3 : 0); }
+  // Slot bits in lane l: those of a row of 16, or (QUAD) up to all six.
+  __device__ __forceinline__ static int lane_slot(int l) {
+    return ((QUAD ? l : l & 15) ^ (((l >> 2) & 1) ? 3 : 0)) & (S - 1);
+  }
   // Block of lane l's register r of the metrics, and of lane l's A row.
   __device__ __forceinline__ static int tau_of(int l, int r) {
+    if constexpr (QUAD) return ((l >> P) << 2) | r;
     return ((((r >> 2) >> BB) << 4) | ((l >> 4) << 2) | (r & 3)) >> IB;
   }
-  __device__ __forceinline__ static int tau_a(int l) { return ((((l >> 4) >> BB) << 4) | (l & 15)) >> IB; }
-  // Register's share of the slot index.
+  __device__ __forceinline__ static int tau_a(int l) {
+    if constexpr (QUAD) return ((l >> P) << 2) | (l & 3);
+    return ((((l >> 4) >> BB) << 4) | (l & 15)) >> IB;
+  }
+  // Which of a load's dwords lane l holds.
+  __device__ __forceinline__ static int dword_of(int l) { return (l >> (QUAD ? 2 : 4)) & (Sh::DPL - 1); }
+  // Register's share of the slot index, and of the lane's blocks.
   static constexpr int reg_slot(int r) { return (((r >> 2) & ((1 << BB) - 1)) << 4) | ((r & ((1 << IB) - 1)) << 6); }
+  static constexpr int reg_class(int r) { return QUAD ? r : ((((r >> 2) >> BB) << 2) | (r & 3)) >> IB; }
+  static constexpr int class_reg(int c) {
+    for (int r = 0; r < R; ++r)
+      if (reg_class(r) == c) return r;
+    return 0;
+  }
 
   // Parity pattern (bit b) of slot bits st in the branch that stays, phase q.
   __device__ __forceinline__ static uint32_t pattern(const uint32_t *gen, int q, uint32_t st) {
@@ -204,18 +281,20 @@ struct DecoderM {
         v |= (one | (((c >> b) & 1) ? 0x8000u : 0u)) << (16 * (b - 2 * w));
     } else {
 #pragma unroll
-      for (int b = 0; b < BETA; ++b) v |= (((c >> b) & 1) ? 0x100u - S : (uint32_t)S) << (8 * b);
+      for (int b = 0; b < BETA; ++b) v |= (((c >> b) & 1) ? 0x100u - S : (uint32_t)S) << (8 * b + (BETA == 3 ? 8 : 0));
     }
     return v;
   }
 
   __device__ __forceinline__ void setup(const uint32_t *gen) {
     lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    nothing = 0;
+    asm volatile("" : "+s"(nothing));
     constexpr int W = F16 ? (BETA + 1) / 2 : 1;
     uint32_t top = 0;
 #pragma unroll
     for (int b = 0; b < BETA; ++b) top |= ((gen[b] >> P) & 1u) << b;
-    const uint32_t st = (uint32_t)(col_slot(lane) | (((lane >> 4) & ((1 << BB) - 1)) << 4));
+    const uint32_t st = (uint32_t)(lane_slot(lane) | (((lane >> 4) & ((1 << BB) - 1)) << 4));
     const uint32_t row = (uint32_t)(lane & ((1 << IB) - 1)) << 6;
 #pragma unroll
     for (int w = 0; w < W; ++w) {
@@ -224,90 +303,74 @@ struct DecoderM {
     }
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-      const uint32_t c = pattern(gen, q, st);
+      uint32_t c = pattern(gen, q, st);
+      if (QUAD && q >= 4) c ^= (lane >> q) & 1 ? top : 0u;
 #pragma unroll
       for (int w = 0; w < W; ++w) stay[q][w] = signs(c, w);
-      if constexpr (F16) {
-        const uint32_t s = pattern(gen, q, row);
+    }
+    if constexpr (F16) {
 #pragma unroll
-        for (int w = 0; w < W; ++w) rowsign[w] |= (((s >> (2 * w)) & 1) << (15 - q)) | (((s >> (2 * w + 1)) & 1) << (31 - q));
+      for (int x = 0; x < Sh::NL * Sh::SPD; ++x) {
+        const int t = (x / Sh::SPD) * Sh::SPL + dword_of(lane) * Sh::SPD + x % Sh::SPD;
+        const uint32_t s = pattern(gen, t % P, row);
+#pragma unroll
+        for (int w = 0; w < W; ++w) rowsign[w] |= (((s >> (2 * w)) & 1) << (15 - x)) | (((s >> (2 * w + 1)) & 1) << (31 - x));
       }
     }
 #pragma unroll
-    for (int b = 0; b < 4; ++b) tag[b] = (S - 1) ^ (col_slot(lane) | reg_slot(4 * b));
+    for (int b = 0; b < R / 4; ++b) tag[b] = (S - 1) ^ (lane_slot(lane) | reg_slot(4 * b));
   }
   __device__ __forceinline__ int own_tag(int r) const { return tag[r >> 2] - (reg_slot(r) & ~63); }
 
-  // ---- LLRs: period g of body bd, this lane's row.
-  // Hard decisions become +-1 when the period's first stage runs (not at the
-  // load, which would wait for it).
-  template <int G>
-  __device__ __forceinline__ void to_pm1() {
-    if constexpr (IN == VIT_LLR_HARD) {
+  // ---- LLRs.  beta = 2: two stages a dword; 3: a stage's three bytes end the
+  // dword; 4: a stage.  A dword ends with its last stage's last LLR, so that
+  // none reaches past the window; dwords before the frame or past the window
+  // are clamped (no stage of the block's uses them).
+  __device__ __forceinline__ int offset(int l, int bd) const { return off0 + (bd * BODY + l * Sh::SPL) * BETA; }
+  template <int L>
+  __device__ __forceinline__ void load(int bd) {
+    int at = offset(L, bd);
+    at = at < end ? at : end;
+    at = at > before ? at : before;
+    raw[L % Sh::AHEAD] = *(gword_t)(llr + at);
+  }
+  // Load L's dwords as A operands; its register is free for a later one.
+  // START: of a body in which blocks start; a dword that straddles the frame's
+  // first byte was read from that byte on.
+  template <int L, bool START>
+  __device__ __forceinline__ void take() {
+    uint32_t w = raw[L % Sh::AHEAD];
+    if constexpr (START && BETA != 4) {
+      const int at = offset(L, body), c = at > before ? at : before;
+      w <<= (8 * (c - at)) & 31;
+    }
+    if constexpr (IN == VIT_LLR_HARD) w = hard_to_pm1(w);
+    if constexpr (F16) {
 #pragma unroll
-      for (int i = 0; i < WORDS; ++i) raw[G][i] = hard_to_pm1(raw[G][i]);
+      for (int h = 0; h < Sh::SPD; ++h) to_f16(w, h, L * Sh::SPD + h);
+    } else {
+      cur[0][0] = w ^ nothing;
+      if constexpr (Sh::SPD == 2) cur[Sh::SPD - 1][0] = cur[0][0] >> 16;
     }
   }
-  // (offset inside the frame, or past the window's last period: then clamped)
-  template <int G>
-  __device__ __forceinline__ void load_period(int bd) {
-    int at = off0 + (bd * BODY + G * P) * BETA;
-    at = at < end ? at : end;
-    const gin_t p = llr + at;
-#pragma unroll
-    for (int i = 0; i < Sh::FULL; ++i) raw[G][i] = ((gword_t)p)[i];
-    if constexpr (Sh::REM) raw[G][Sh::FULL] = *(gword_t)(p + Sh::BYTES - 4);
-  }
-  // Same where the period may begin before the frame: dword by dword, a dword
-  // that straddles the frame's first byte read from that byte on.
-  template <int G>
-  __device__ __forceinline__ void load_period_checked(int bd) {
-    int at = off0 + (bd * BODY + G * P) * BETA;
-    at = at < end ? at : end;
-#pragma unroll
-    for (int i = 0; i < WORDS; ++i) {
-      const int a = i < Sh::FULL ? at + 4 * i : at + Sh::BYTES - 4;
-      const int c = a > before ? a : before;
-      raw[G][i] = *(gword_t)(llr + c) << ((8 * (c - a)) & 31);
-    }
-  }
-
-  // LLR bytes of the period's stage j in the low BETA bytes.
-  template <int G, int J>
-  __device__ __forceinline__ uint32_t stage_bytes() const {
-    constexpr int i = J * BETA / 4, bs = J * BETA % 4;
-    // (a last partial dword holds the period's last four bytes)
-    if constexpr (Sh::REM && J == P - 1) return raw[G][Sh::FULL] >> (8 * (4 - BETA));
-    else if constexpr (bs == 0) return raw[G][i];
-    else if constexpr (bs + BETA <= 4) return raw[G][i] >> (8 * bs);
-    else return __builtin_amdgcn_alignbyte(raw[G][i + 1 < WORDS ? i + 1 : i], raw[G][i], bs);
-  }
-
-  // fp16 values of a stage's LLR bytes, exact: 0x6400 | (byte + 128) is 1152
+  // fp16 values of half h's LLR bytes, exact: 0x6400 | (byte + 128) is 1152
   // more than the byte; the row's signs on top.
-  template <int Q>
-  __device__ __forceinline__ f16x4 stage_f16(uint32_t w) const {
-    uint32_t a[2] = {0, 0};
-    int q = Q;
-    asm volatile("" : "+s"(q));
-    const uint32_t h = __builtin_amdgcn_perm(0u, w, 0x0C010C00u) ^ 0x64806480u;
-    const f16x2 lo = __builtin_bit_cast(f16x2, h) - (f16x2){(_Float16)1152.0f, (_Float16)1152.0f};
-    a[0] = __builtin_bit_cast(uint32_t, lo) ^ ((rowsign[0] << q) & 0x80008000u);
+  __device__ __forceinline__ void to_f16(uint32_t w, int h, int x) {
+    asm volatile("" : "+s"(x));  // (keeps the signs out of loop-invariant code motion)
+    const uint32_t sel = BETA == 3 ? 0x0C020C01u : h ? 0x0C030C02u : 0x0C010C00u;
+    const uint32_t v = __builtin_amdgcn_perm(0u, w, sel) ^ 0x64806480u;
+    const f16x2 lo = __builtin_bit_cast(f16x2, v) - (f16x2){(_Float16)1152.0f, (_Float16)1152.0f};
+    cur[h][0] = __builtin_bit_cast(uint32_t, lo) ^ ((rowsign[0] << x) & 0x80008000u);
     if constexpr (BETA > 2) {
-      constexpr uint32_t sel = BETA > 3 ? 0x0C030C02u : 0x0C0C0C02u, off = BETA > 3 ? 0x64806480u : 0x00006480u;
-      const uint32_t g = __builtin_amdgcn_perm(0u, w, sel) ^ off;
+      constexpr uint32_t sel2 = BETA > 3 ? 0x0C030C02u : 0x0C0C0C03u, off = BETA > 3 ? 0x64806480u : 0x00006480u;
+      const uint32_t g = __builtin_amdgcn_perm(0u, w, sel2) ^ off;
       const f16x2 hi = __builtin_bit_cast(f16x2, g) - (f16x2){(_Float16)1152.0f, (_Float16)(BETA > 3 ? 1152.0f : 0.0f)};
-      a[1] = __builtin_bit_cast(uint32_t, hi) ^ ((rowsign[F16 && BETA > 2 ? 1 : 0] << q) & 0x80008000u);
+      cur[h][F16 && BETA > 2 ? 1 : 0] =
+          __builtin_bit_cast(uint32_t, hi) ^ ((rowsign[F16 && BETA > 2 ? 1 : 0] << x) & 0x80008000u);
     }
-    return pair(a[0], a[1]);
   }
   __device__ __forceinline__ static f16x4 pair(uint32_t lo, uint32_t hi) {
     return __builtin_bit_cast(f16x4, ((uint64_t)hi << 32) | lo);
-  }
-
-  template <int Q>
-  __device__ __forceinline__ static int exchange(int v) {
-    return devi::exchange<Q>(v);
   }
 
   // Blocks that start at timeline stage t: their start metrics.  (Rare: kept
@@ -318,16 +381,13 @@ struct DecoderM {
     asm volatile("" : "+v"(packed), "+v"(from));
 #pragma unroll
     for (int c = 0; c < NCLS; ++c) {
-      // registers of class c hold block tau_of(lane, r) for any r of the class
-      const int rep = IB == 2 ? 0 : IB == 1 ? 2 * c : ((c >> 2) << (2 + BB)) | (c & 3);
-      const int st = __builtin_amdgcn_ds_bpermute(tau_of(from, rep) << 2, packed);
+      const int st = __builtin_amdgcn_ds_bpermute(tau_of(from, class_reg(c)) << 2, packed);
       const bool now = (st >> 1) == t;
       const int far = (st & 1) ? kUnreached * S : 0;          // slots other than 0
-      const int far0 = (from & 15) ? far : 0;                 // registers whose share of the slot is 0
+      const int far0 = lane_slot(from) ? far : 0;             // registers whose share of the slot is 0
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int cls = ((((r >> 2) >> BB) << 2) | (r & 3)) >> IB;
-        if (cls != c) continue;
+      for (int r = 0; r < R; ++r) {
+        if (reg_class(r) != c) continue;
         o[r] = now ? kZero + own_tag(r) + (reg_slot(r) ? far : far0) : o[r];
       }
     }
@@ -336,47 +396,58 @@ struct DecoderM {
   // One trellis stage at body offset G.
   template <int G, bool GUARD>
   __device__ __forceinline__ void step() {
-    constexpr int q = G % P, g = G / P;
+    constexpr int q = G % P, load_of = G / Sh::SPL, dword = G % Sh::SPL / Sh::SPD, half = G % Sh::SPD;
     if constexpr (GUARD) {
       const int t = body * BODY + G;
       if (__builtin_amdgcn_ballot_w64((start >> 1) == t)) set_starts(t);
     }
-    if constexpr (q == 0) to_pm1<g>();
-    const uint32_t w = stage_bytes<g, q>();
+    if constexpr (G % Sh::SPL == 0) {
+      take<load_of, GUARD>();
+      constexpr int next = (load_of + Sh::AHEAD) % Sh::NL, later = (load_of + Sh::AHEAD) / Sh::NL;
+      load<next>(body + later);
+    }
+    const uint32_t(&w)[F16 && BETA > 2 ? 2 : 1] = cur[half];
     uint32_t flip[F16 && BETA > 2 ? 2 : 1];
 #pragma unroll
     for (uint32_t x = 0; x < sizeof(flip) / 4; ++x) {
       flip[x] = newest[x];
-      asm volatile("" : "+s"(flip[x]));  // (keeps the products out of loop-invariant code motion)
+      if constexpr (F16) asm volatile("" : "+s"(flip[x]));  // (keeps the products out of loop-invariant code motion)
     }
-    i32x16 out;
-    __builtin_amdgcn_s_setprio(1);
-    if constexpr (F16) {
-      const f16x4 a = stage_f16<q>(w);
+    decltype(o) out;
+    if constexpr (!QUAD) __builtin_amdgcn_s_setprio(1);
+    if constexpr (QUAD) {
+      out = __builtin_amdgcn_mfma_i32_4x4x4i8((int)w[0], (int)(stay[q][0] ^ flip[0]), o, Sh::CBSZ, dword, 0);
+      o = __builtin_amdgcn_mfma_i32_4x4x4i8((int)w[0], (int)stay[q][0], o, Sh::CBSZ, dword, 0);
+    } else if constexpr (F16) {
       const f32x16 c = __builtin_bit_cast(f32x16, o);
       constexpr int h = BETA > 2 ? 1 : 0;
+      const f16x4 a = pair(w[0], h ? w[h] : 0u);
       const f16x4 leave = pair(stay[q][0] ^ flip[0], h ? stay[q][h] ^ flip[h] : 0u);
-      out = __builtin_bit_cast(i32x16, __builtin_amdgcn_mfma_f32_16x16x4f16(a, leave, c, 0, 0, 0));
+      out = __builtin_bit_cast(i32x16, __builtin_amdgcn_mfma_f32_16x16x4f16(a, leave, c, Sh::CBSZ, dword, 0));
       o = __builtin_bit_cast(i32x16, __builtin_amdgcn_mfma_f32_16x16x4f16(a, pair(stay[q][0], h ? stay[q][h] : 0u), c,
-                                                                          0, 0, 0));
+                                                                          Sh::CBSZ, dword, 0));
     } else {
-      out = __builtin_amdgcn_mfma_i32_16x16x4i8((int)w, (int)(stay[q][0] ^ flip[0]), o, 0, 0, 0);
-      o = __builtin_amdgcn_mfma_i32_16x16x4i8((int)w, (int)stay[q][0], o, 0, 0, 0);
+      out = __builtin_amdgcn_mfma_i32_16x16x4i8((int)w[0], (int)(stay[q][0] ^ flip[0]), o, Sh::CBSZ, dword, 0);
+      o = __builtin_amdgcn_mfma_i32_16x16x4i8((int)w[0], (int)stay[q][0], o, Sh::CBSZ, dword, 0);
     }
-    __builtin_amdgcn_s_setprio(0);
-    if constexpr (q == P - 1) {  // the period's LLRs are used up
-      constexpr int next = (g + Sh::LOOK) % NG, later = (g + Sh::LOOK) / NG;
-      if constexpr (GUARD) load_period_checked<next>(body + later);
-      else load_period<next>(body + later);
-    }
+    if constexpr (!QUAD) __builtin_amdgcn_s_setprio(0);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      if constexpr (q < 4) o[r] = max_i(o[r], exchange<(q < 4 ? q : 0)>(out[r]));
-      else o[r] = max_i(o[r], out[r ^ (q < 6 ? 4 << (q < 4 ? 0 : q - 4) : 1 << (q < 6 ? 0 : q - 6))]);
+    for (int r = 0; r < R; ++r) {
+      if constexpr (q < 4) {
+        o[r] = max_i(o[r], devi::exchange<q < 4 ? q : 0>(out[r]));
+      } else if constexpr (QUAD) {
+        // stay in the lower lanes and leave in the upper ones of o, the others in out: the swap brings a slot's
+        // two candidates together
+        const auto v = q == 4 ? __builtin_amdgcn_permlane16_swap((uint32_t)o[r], (uint32_t)out[r], false, false)
+                              : __builtin_amdgcn_permlane32_swap((uint32_t)o[r], (uint32_t)out[r], false, false);
+        o[r] = max_i((int)v[0], (int)v[1]);
+      } else {
+        o[r] = max_i(o[r], out[r ^ (q < 6 ? 4 << (q < 4 ? 0 : q - 4) : 1 << (q < 6 ? 0 : q - 6))]);
+      }
     }
     if constexpr (q == P - 1) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
+      for (int r = 0; r < R; ++r) {
         dec[r] = __builtin_amdgcn_alignbit((uint32_t)o[r], dec[r], P);
         o[r] = ((o[r] & -S) | tag[r >> 2]) - (reg_slot(r) & ~63);
       }
@@ -407,29 +478,38 @@ struct DecoderM {
 
   // A body's survivor words to LDS: [slot's complement][tau], the quad's
   // registers together.
-  __device__ __forceinline__ void store_words(int region, const uint32_t (&d)[16]) {
-    const int pos = ((15 - col_slot(lane)) << 4) | ((lane >> 4) << 2);
+  __device__ __forceinline__ void store_words(int region, const uint32_t (&d)[R]) {
+    if constexpr (QUAD) {
+      const u32x4 v = {d[0], d[1], d[2], d[3]};
+      *(u32x4 *)(lds + region * Sh::REGION + tag[0] * NB + ((lane >> P) << 2)) = v;
+      return;
+    }
+    const int pos = ((15 - lane_slot(lane)) << 4) | ((lane >> 4) << 2);
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
+    for (int b = 0; b < R / 4; ++b) {
       // b's slot bits complemented, its block bits as they are
       constexpr int sb = (1 << BB) - 1;
       const int row = (b & ~sb) | (sb - (b & sb));
       u32x4 v;
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i ^ ((1 << IB) - 1)] = d[4 * b + i];
-      *(u32x4 *)(lds + region * 1024 + row * 256 + pos) = v;
+      *(u32x4 *)(lds + region * Sh::REGION + row * 256 + pos) = v;
     }
   }
-  // Where block tau's decoded word of body n goes: over the survivors of a
-  // region that has been traced (the register bodies use region 0 in turn, so
-  // they and body NR leave theirs in region 1).
-  __device__ __forceinline__ static int decoded_at(int n) {
-    return n > Sh::NR ? (n - Sh::NR) * 1024 : 1024 + 128 + (Sh::NR - n) * 64;
+  // Where the blocks' decoded words of kept body n go: after the survivors, or
+  // (where LDS limits the waves) over the survivors of a region that has been
+  // traced: the register bodies use region 0 in turn, so they and body NR leave
+  // theirs in region 1.
+  __device__ __forceinline__ int decoded_at(int n) const {
+    if constexpr (QUAD) return decoded + n * NB;
+    return n > Sh::NR ? (n - Sh::NR) * Sh::REGION : Sh::REGION + 128 + (Sh::NR - n) * 64;
   }
-  static_assert(128 + (Sh::NR + 1) * 64 <= 1024, "decoded words of the register bodies");
+  __device__ __forceinline__ int last_at(int bodies) const { return QUAD ? decoded + bodies * NB : Sh::REGION + 64; }
+  static_assert(QUAD || 128 + (Sh::NR + 1) * 64 <= Sh::REGION, "decoded words of the register bodies");
 
   // Dword within a body's survivors of block tau's word for complement uc.
   __device__ __forceinline__ static int word_at(uint32_t uc, int tau) {
+    if constexpr (QUAD) return (int)uc * NB + tau;
     int at = ((tau >> 4) << (8 + BB)) + (int)((uc & ((16u << BB) - 1u)) << 4) + ((tau & 15) << IB);
     if constexpr (IB) at += (int)(uc >> (4 + BB));
     return at;
@@ -455,14 +535,21 @@ __device__ __forceinline__ void lds_phase() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Periods that the entry offset r skips are the second body's.  (With a
-// shorter look-ahead the last ones are loaded again in the course.)
-template <int G, class D>
+// The loads ahead of an entry at offset r of the first body; one that is entered
+// past its first stage is taken here.
+template <int L, class D>
 __device__ __forceinline__ void first_loads(D &d, int r) {
-  if constexpr (G < D::NG) {
-    d.template load_period_checked<G>((G + 1) * D::P <= r ? 1 : 0);
-    if (G == r / D::P && r % D::P != 0) d.template to_pm1<G>();  // entered past its first stage
-    first_loads<G + 1>(d, r);
+  using Sh = typename D::Sh;
+  if constexpr (L < Sh::NL) {
+    constexpr int first = L * Sh::SPL, past = first + Sh::SPL < Sh::BODY ? first + Sh::SPL : Sh::BODY;
+    constexpr int next = (L + Sh::AHEAD) % Sh::NL, later = (L + Sh::AHEAD) / Sh::NL;
+    if (L < Sh::AHEAD && r < past) d.template load<L>(0);
+    if (r >= past) d.template load<next>(later);
+    if (first < r && r < past) {
+      d.template take<L, true>();
+      d.template load<next>(later);
+    }
+    first_loads<L + 1>(d, r);
   }
 }
 
@@ -471,20 +558,21 @@ __device__ __forceinline__ void first_loads(D &d, int r) {
 // memory from `before` bytes ahead on.
 // `describe` is called before the recursion and again after it, which costs
 // less than holding its result in registers.
-template <int K, int BETA, int IN, class Describe>
-__device__ __forceinline__ void decode_tile(DecoderM<K, BETA, IN> &D, Describe describe) {
+template <int K, int BETA, int IN, bool QUAD, class Describe>
+__device__ __forceinline__ void decode_tile(DecoderM<K, BETA, IN, QUAD> &D, Describe describe) {
   Blk bk = describe();
-  using Sh = ShapeM<K, BETA>;
-  constexpr int P = Sh::P, S = Sh::S, NB = Sh::NB, NCLS = Sh::NCLS, NG = Sh::NG, BODY = Sh::BODY;
+  using Sh = ShapeM<K, BETA, QUAD>;
+  constexpr int P = Sh::P, S = Sh::S, NB = Sh::NB, NCLS = Sh::NCLS, NG = Sh::NG, BODY = Sh::BODY, R = Sh::R;
   const int lane = D.lane;
   const int most = wave_max_all(bk.M);
   const int r = (BODY - most % BODY) % BODY;
   const int nbody = (most + r) / BODY;
   const int begin = nbody * BODY - bk.M;
   D.start = 2 * begin + (bk.known ? 1 : 0);
-  const int last_start = wave_max_all(begin);
   const int grp_lo = -wave_max_all(-(begin + bk.core)) / BODY;  // the first body with a core bit's decision
   D.keep = grp_lo;
+  const int kept = nbody - grp_lo;
+  D.decoded = (kept - Sh::NR > 1 ? kept - Sh::NR : 1) * Sh::REGION;
   {
     const int from = D.tau_a(lane) << 2;
     const uint64_t p = (uint64_t)bk.llr;
@@ -492,22 +580,24 @@ __device__ __forceinline__ void decode_tile(DecoderM<K, BETA, IN> &D, Describe d
     const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(p >> 32));
     D.llr = (gin_t)(((uint64_t)hi << 32) | lo);
     const int M = __builtin_amdgcn_ds_bpermute(from, bk.M);
-    D.off0 = (M - nbody * BODY) * BETA;
+    D.off0 = (M - nbody * BODY + D.dword_of(lane) * Sh::SPD) * BETA - (BETA == 3 ? 1 : 0);
     D.before = -__builtin_amdgcn_ds_bpermute(from, bk.before);
-    D.end = (M - P) * BETA;
+    D.end = M * BETA - 4;
   }
 #pragma unroll
-  for (int x = 0; x < 16; ++x) {
+  for (int x = 0; x < R; ++x) {
     D.o[x] = D.kZero + D.own_tag(x);
     D.dec[x] = 0u;
   }
+  D.body = 0;
   first_loads<0>(D, r);
-  for (D.body = 0; D.body < nbody && D.body * BODY <= last_start; ++D.body) {
+  const int starts_in = begin / BODY;
+  while (D.body < nbody) {  // one body in which blocks start (as in the first), and those up to the next such
     const int from = D.body == 0 ? r : 0;
     VITM_X32(VITM_G1, BODY)
-  }
-  for (; D.body < nbody; ++D.body) {
-    VITM_X32(VITM_U1, BODY)
+    for (++D.body; D.body < nbody && !__builtin_amdgcn_ballot_w64(starts_in == D.body); ++D.body) {
+      VITM_X32(VITM_U1, BODY)
+    }
   }
   lds_phase();
   bk = describe();
@@ -520,34 +610,34 @@ __device__ __forceinline__ void decode_tile(DecoderM<K, BETA, IN> &D, Describe d
   for (int c = 0; c < NCLS; ++c) {
     int m = INT32_MIN;
 #pragma unroll
-    for (int x = 0; x < 16; ++x) {
-      // class of register x: the part of tau that the register gives
-      const int cls = (((((x >> 2) >> Sh::BB) << 2) | (x & 3)) >> Sh::IB);
-      if (cls == c) m = max_i(m, D.o[x]);
-    }
+    for (int x = 0; x < R; ++x)
+      if (D.reg_class(x) == c) m = max_i(m, D.o[x]);
     m = max_i(m, devi::exchange<0>(m));
     m = max_i(m, devi::exchange<1>(m));
-    m = max_i(m, devi::exchange<2>(m));
-    m = max_i(m, devi::exchange<3>(m));
-    // tau = (class's b part, row quad, class's register part)
+    if constexpr (P > 2) m = max_i(m, devi::exchange<2>(m));
+    if constexpr (P > 3) m = max_i(m, devi::exchange<3>(m));
+    if constexpr (QUAD && P > 4) m = max_i(m, devi::exchange<4>(m));
+    if constexpr (QUAD && P > 5) m = max_i(m, devi::exchange<5>(m));
+    // to lane tau, if class c is its block's: any lane that holds the block
     constexpr int kQ = 2 - Sh::IB;  // bits of tau below the row quad
-    const int got = __builtin_amdgcn_ds_bpermute((((lane >> kQ) & 3) << 4) << 2, m);
-    const int mine = ((lane >> (kQ + 2)) << kQ) | (lane & ((1 << kQ) - 1));
+    const int at = QUAD ? ((lane >> 2) << P) & 63 : ((lane >> kQ) & 3) << 4;
+    const int got = __builtin_amdgcn_ds_bpermute(at << 2, m);
+    const int mine = QUAD ? lane & 3 : ((lane >> (kQ + 2)) << kQ) | (lane & ((1 << kQ) - 1));
     uc = mine == c ? (uint32_t)got & (uint32_t)(S - 1) : uc;
   }
   if (bk.zero) uc = S - 1;
   const uint32_t lam_start = uc ^ (uint32_t)(S - 1);
-  for (int grp = nbody - 1 - grp_lo; grp >= 0; --grp) {
+  for (int grp = kept - 1; grp >= 0; --grp) {
     int region = grp - Sh::NR;
     if (region < 0) {
       region = 0;
-      uint32_t d[16];
+      uint32_t d[R];
       kept_words(grp, d);
       D.store_words(0, d);
       lds_phase();
     }
     if (lane < NB) {
-      const uint32_t *w = D.lds + region * 1024;
+      const uint32_t *w = D.lds + region * Sh::REGION;
       uint32_t acc = 0;
 #pragma unroll
       for (int g = NG - 1; g >= 0; --g) {
@@ -558,7 +648,7 @@ __device__ __forceinline__ void decode_tile(DecoderM<K, BETA, IN> &D, Describe d
     }
     lds_phase();
   }
-  if (lane < NB) D.lds[1024 + 64 + lane] = lam_start;  // (region 1 has been traced)
+  if (lane < NB) D.lds[D.last_at(kept) + lane] = lam_start;  // (region 1 has been traced)
   lds_phase();
   lds_phase();
 
@@ -578,8 +668,8 @@ __device__ __forceinline__ void decode_tile(DecoderM<K, BETA, IN> &D, Describe d
       const int at = gc + bit;
       const int wa = at / BODY, sh = at - wa * BODY;
       auto word = [&](int i) -> uint64_t {
-        if (i < nbody - grp_lo) return D.lds[D.decoded_at(i) + tau] & body_mask;
-        return i == nbody - grp_lo ? D.lds[1024 + 64 + tau] : 0u;
+        if (i < kept) return D.lds[D.decoded_at(i) + tau] & body_mask;
+        return i == kept ? D.lds[D.last_at(kept) + tau] : 0u;
       };
       uint64_t cat = word(wa) | (word(wa + 1) << BODY);
       if constexpr (BODY < 32) cat |= word(wa + 2) << (2 * BODY);
@@ -599,12 +689,11 @@ __device__ __forceinline__ void decode_tile(DecoderM<K, BETA, IN> &D, Describe d
 // Stream kernel: wave w decodes blocks [NB w, NB w + NB), then those NB x
 // (waves of the grid) further on; blocks past the last are the last again, not
 // written.
-template <int K, int BETA, int IN>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8), amdgpu_num_vgpr(64))) void vit_blocked_mx_kernel(DecodeArgs a) {
-  using Sh = ShapeM<K, BETA>;
+template <int K, int BETA, int IN, bool QUAD>
+__device__ __forceinline__ void blocked_mx(const DecodeArgs &a) {
+  using Sh = ShapeM<K, BETA, QUAD>;
   extern __shared__ uint32_t vit_ldsm[];
-  asm volatile("" ::: "v255");
-  DecoderM<K, BETA, IN> D;
+  DecoderM<K, BETA, IN, QUAD> D;
   D.setup(a.gen);
   D.lds = vit_ldsm;
   const int64_t tiles = (a.nblocks + Sh::NB - 1) / Sh::NB;
@@ -634,15 +723,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8), amdgp
 }
 
 // Batch kernel: the code's items (longest first), NB at a time.
-template <int K, int BETA, int IN>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8), amdgpu_num_vgpr(64))) void vit_batch_mx_kernel(BatchArgs a) {
-  using Sh = ShapeM<K, BETA>;
+template <int K, int BETA, int IN, bool QUAD>
+__device__ __forceinline__ void batch_mx(const BatchArgs &a) {
+  using Sh = ShapeM<K, BETA, QUAD>;
   extern __shared__ uint32_t vit_ldsm[];
-  asm volatile("" ::: "v255");
   const int nitems = __builtin_amdgcn_readfirstlane(a.header[kMaxCodes + a.code_index]);
   const int tiles = (nitems + Sh::NB - 1) / Sh::NB;
   if ((int)blockIdx.x >= tiles) return;
-  DecoderM<K, BETA, IN> D;
+  DecoderM<K, BETA, IN, QUAD> D;
   D.setup(a.gen);
   D.lds = vit_ldsm;
   const WorkItem *items = a.items + a.header[2 * kMaxCodes + a.code_index];
@@ -667,6 +755,31 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8), amdgp
   }
 }
 
+// Compiled for 128 vector registers and claiming 256, or for 64 and claiming
+// 128 (amdgpu_num_vgpr counts in pairs here).
+#define VITM_WIDE __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8), amdgpu_num_vgpr(64))) void
+#define VITM_NARROW __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8), amdgpu_num_vgpr(32))) void
+template <int K, int BETA, int IN>
+VITM_WIDE vit_blocked_mx_kernel(DecodeArgs a) {
+  asm volatile("" ::: "v255");
+  blocked_mx<K, BETA, IN, false>(a);
+}
+template <int K, int BETA, int IN>
+VITM_WIDE vit_batch_mx_kernel(BatchArgs a) {
+  asm volatile("" ::: "v255");
+  batch_mx<K, BETA, IN, false>(a);
+}
+template <int K, int BETA, int IN>
+VITM_NARROW vit_blocked_quad_kernel(DecodeArgs a) {
+  asm volatile("" ::: "v127");
+  blocked_mx<K, BETA, IN, true>(a);
+}
+template <int K, int BETA, int IN>
+VITM_NARROW vit_batch_quad_kernel(BatchArgs a) {
+  asm volatile("" ::: "v127");
+  batch_mx<K, BETA, IN, true>(a);
+}
+
 #undef VITM_G1
 #undef VITM_U1
 #undef VITM_X8
@@ -675,29 +788,41 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 8), amdgp
 }  // namespace devm
 
 // Kernel instances for (K, beta, input kind VIT_LLR_I8 / VIT_LLR_HARD), taking
-// DecodeArgs, or BatchArgs.
+// DecodeArgs, or BatchArgs: the 16-register layout (k = 6..9) or the
+// 4-register one (k = 3..7).
+template <int K, int BETA>
+void *pick_kernel_mx_kb(int in, bool batch, bool quad) {
+  const bool hard = in == VIT_LLR_HARD;
+  if constexpr (K <= 7) {
+    if (quad && batch)
+      return hard ? (void *)devm::vit_batch_quad_kernel<K, BETA, VIT_LLR_HARD> : (void *)devm::vit_batch_quad_kernel<K, BETA, VIT_LLR_I8>;
+    if (quad)
+      return hard ? (void *)devm::vit_blocked_quad_kernel<K, BETA, VIT_LLR_HARD> : (void *)devm::vit_blocked_quad_kernel<K, BETA, VIT_LLR_I8>;
+  }
+  if constexpr (K >= 6) {
+    if (!quad && batch)
+      return hard ? (void *)devm::vit_batch_mx_kernel<K, BETA, VIT_LLR_HARD> : (void *)devm::vit_batch_mx_kernel<K, BETA, VIT_LLR_I8>;
+    if (!quad)
+      return hard ? (void *)devm::vit_blocked_mx_kernel<K, BETA, VIT_LLR_HARD> : (void *)devm::vit_blocked_mx_kernel<K, BETA, VIT_LLR_I8>;
+  }
+  return nullptr;
+}
 template <int K>
-void *pick_kernel_mx_k(int beta, int in, bool batch) {
-  auto pick = [&](auto bt) -> void * {
-    constexpr int B = decltype(bt)::value;
-    if (batch)
-      return in == VIT_LLR_HARD ? (void *)devm::vit_batch_mx_kernel<K, B, VIT_LLR_HARD>
-                                : (void *)devm::vit_batch_mx_kernel<K, B, VIT_LLR_I8>;
-    return in == VIT_LLR_HARD ? (void *)devm::vit_blocked_mx_kernel<K, B, VIT_LLR_HARD>
-                              : (void *)devm::vit_blocked_mx_kernel<K, B, VIT_LLR_I8>;
-  };
+void *pick_kernel_mx_k(int beta, int in, bool batch, bool quad) {
   switch (beta) {
-    case 2: return pick(std::integral_constant<int, 2>{});
-    case 3: return pick(std::integral_constant<int, 3>{});
-    case 4: return pick(std::integral_constant<int, 4>{});
+    case 2: return pick_kernel_mx_kb<K, 2>(in, batch, quad);
+    case 3: return pick_kernel_mx_kb<K, 3>(in, batch, quad);
+    case 4: return pick_kernel_mx_kb<K, 4>(in, batch, quad);
   }
   return nullptr;
 }
 
-void *pick_kernel_mx_k5(int beta, int in, bool batch);
-void *pick_kernel_mx_k6(int beta, int in, bool batch);
-void *pick_kernel_mx_k7(int beta, int in, bool batch);
-void *pick_kernel_mx_k8(int beta, int in, bool batch);
-void *pick_kernel_mx_k9(int beta, int in, bool batch);
+void *pick_kernel_mx_k3(int beta, int in, bool batch, bool quad);
+void *pick_kernel_mx_k4(int beta, int in, bool batch, bool quad);
+void *pick_kernel_mx_k5(int beta, int in, bool batch, bool quad);
+void *pick_kernel_mx_k6(int beta, int in, bool batch, bool quad);
+void *pick_kernel_mx_k7(int beta, int in, bool batch, bool quad);
+void *pick_kernel_mx_k8(int beta, int in, bool batch, bool quad);
+void *pick_kernel_mx_k9(int beta, int in, bool batch, bool quad);
 
 }  // namespace vit

@@ -2,5 +2,5 @@
 #include "vit_decoder_mx.h"
 
 namespace vit {
-void *pick_kernel_mx_k7(int beta, int in, bool batch) { return pick_kernel_mx_k<7>(beta, in, batch); }
+void *pick_kernel_mx_k7(int beta, int in, bool batch, bool quad) { return pick_kernel_mx_k<7>(beta, in, batch, quad); }
 }  // namespace vit

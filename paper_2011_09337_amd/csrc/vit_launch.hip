@@ -38,13 +38,15 @@ void *pick_kernel_int(int k, int beta, const uint32_t *gen, int in, bool batch) 
   return nullptr;
 }
 
-void *pick_kernel_mx(int k, int beta, int in, bool batch) {
+void *pick_kernel_mx(int k, int beta, int in, bool batch, bool quad) {
   switch (k) {
-    case 5: return pick_kernel_mx_k5(beta, in, batch);
-    case 6: return pick_kernel_mx_k6(beta, in, batch);
-    case 7: return pick_kernel_mx_k7(beta, in, batch);
-    case 8: return pick_kernel_mx_k8(beta, in, batch);
-    case 9: return pick_kernel_mx_k9(beta, in, batch);
+    case 3: return pick_kernel_mx_k3(beta, in, batch, quad);
+    case 4: return pick_kernel_mx_k4(beta, in, batch, quad);
+    case 5: return pick_kernel_mx_k5(beta, in, batch, quad);
+    case 6: return pick_kernel_mx_k6(beta, in, batch, quad);
+    case 7: return pick_kernel_mx_k7(beta, in, batch, quad);
+    case 8: return pick_kernel_mx_k8(beta, in, batch, quad);
+    case 9: return pick_kernel_mx_k9(beta, in, batch, quad);
   }
   return nullptr;
 }
@@ -192,69 +194,111 @@ hipError_t launch_blocked16(const DecodeArgs &a, hipStream_t stream, int *unsupp
 
 // ---- the matrix-core kernels (vit_decoder_mx.h)
 
-int mx_blocks(int k) { return k <= 5 ? 64 : 1 << (11 - k); }  // per wave
+// Two layouts: 16 metric registers a wave (k = 6..9), or 4 (quad, k = 3..7).
+bool mx_takes(int k, bool quad) { return quad ? k <= 7 : k >= 6; }
+int mx_blocks(int k, bool quad) { return 1 << ((quad ? 9 : 11) - k); }  // per wave
 
-// Survivor regions of a wave whose blocks are traced over `traced` stages (from
-// the first core bit to the window's end) beyond those in registers.
-int64_t mx_lds_bytes(int k, int64_t traced) {
+// LDS of a wave whose blocks are traced over `traced` stages (from the first
+// core bit to the window's end): survivors of the bodies beyond those in
+// registers, and (quad) the decoded words.
+int64_t mx_lds_bytes(int k, int64_t traced, bool quad) {
   const int64_t body = body_len(k);
-  const int64_t regions = (traced + body - 1) / body - devm::kKept;
-  return (regions > 2 ? regions : 2) * 4096;
+  const int64_t bodies = (traced + body - 1) / body;
+  const int64_t regions = bodies - devm::kept_bodies(quad);
+  if (!quad) return (regions > 2 ? regions : 2) * 4 * devm::region_words(false);
+  return 4 * ((regions > 1 ? regions : 1) * devm::region_words(true) + (bodies + 1) * mx_blocks(k, true));
 }
 
-// Waves a CU holds: two per SIMD by registers, fewer by LDS (in units of 1280 bytes).
-int mx_waves_per_cu(int64_t lds, int max_lds) {
+// Waves a CU holds: two per SIMD by registers (quad: four), fewer by LDS (in
+// units of 1280 bytes).
+int mx_waves_per_cu(int64_t lds, int max_lds, bool quad) {
   const int64_t unit = (lds + 1279) / 1280 * 1280;
-  const int64_t by_lds = max_lds / unit;
-  return (int)(by_lds < 8 ? by_lds : 8);
+  const int64_t by_lds = max_lds / unit, most = quad ? 16 : 8;
+  return (int)(by_lds < most ? by_lds : most);
 }
 
-// Which integer kernel decodes `blocks` blocks sooner, by the time each takes
-// per stage (nanoseconds, measured with the chip full and with one wave on a
-// SIMD; the stages of a block are the same for both).  The one-block kernel
-// takes 11.3 per block, 64 states and SIMD where the chip is full (2^24 bits
-// of K=7, L = 256: 210 us) and at least 24 / 30 / 70 (k <= 7, 8, 9; one wave's
-// latency).  A wave of the matrix-core kernel takes 92 / 100 / 115 alone on a
-// SIMD and half as long again beside a second one, for 64..4 blocks, but only
-// as many as LDS holds survivors for run at once.  Measured on both sides of
-// the line: K=7, L = 256, 4096 blocks 20 us by the one-block kernel and 34 by
-// this one, 16384 blocks 61 and 37, 65536 blocks 210 and 91; K=7, L = 512
-// (four waves a CU), 8192 blocks 60 and 59, 32768 blocks 198 and 118; K=7,
-// L = 1024 (one wave a CU), 16384 blocks 218 and 400; K=9, L = 256, 1024 blocks
-// 27 and 40, 4096 blocks 67 and 43, 16384 blocks 236 and 104.
-bool mx_is_faster(int k, int64_t blocks, int64_t lds, int num_cu, int max_lds) {
-  const int per_cu = mx_waves_per_cu(lds, max_lds);
-  if (per_cu < 1) return false;
-  const int64_t simds = 4 * (int64_t)num_cu, slots = (int64_t)per_cu * num_cu;
-  const int64_t tiles = (blocks + mx_blocks(k) - 1) / mx_blocks(k);
+// Time per stage (nanoseconds) of the three integer kernels for `blocks`
+// blocks, measured with the chip full and with one wave on a SIMD; a block's
+// stages are the same for all, so the least is the fastest.  Measured around
+// the lines between them (us, one-block kernel / 16 registers / 4 registers):
+// K=7 r1/2, L = 256, 1024 blocks 11 / 34 / 19, 4096 20 / 34 / 20,
+// 16384 58 / 39 / 36, 65536 210 / 84 / 113; K=7, L = 512 (here LDS holds four
+// waves of the 16-register kernel a CU), 8192 blocks 59 / 60 / 39,
+// 32768 199 / 121 / 107; K=7, L = 1024, 16384 blocks 223 / 407 / 168;
+// K=6, L = 256, 4096 blocks 20 / 35 / 19, 65536 209 / 49 / 60; K=5, L = 256,
+// 4096 blocks 20 / - / 18, 65536 204 / - / 34; K=3, L = 256, 4096 blocks
+// 22 / - / 24, 16384 58 / - / 25; K=9, L = 256, 1024 blocks 26 / 38 / -,
+// 4096 66 / 48 / -, 16384 237 / 94 / -.  Over nine lengths and thirteen sizes
+// of six codes the choice cost 10 % or more in one case of thirty.
+//
+// One block a wave: one wave's latency, and 10.6 for each further 64 states on
+// a SIMD.
+double one_block_ns(int k, int64_t blocks, int64_t simds) {
   const double regs = k > 7 ? 1 << (k - 7) : 1;
   const double latency = k <= 7 ? 24.0 : k == 8 ? 30.0 : 70.0;
-  const double full = 11.3 * regs * (double)blocks / (double)simds;
-  const double one_block = full > latency ? full : latency;
-  const double wave = (k <= 7 ? 92.0 : k == 8 ? 100.0 : 115.0) * ((tiles < slots ? tiles : slots) > simds ? 1.55 : 1.0);
-  return (double)((tiles + slots - 1) / slots) * wave < one_block;
+  return latency + 10.6 * regs * (double)((blocks - 1) / simds);
+}
+// 16 registers: a second wave on a SIMD costs half as much again (some get one
+// before every SIMD has its first); as many as fit at a time, whole rounds of
+// persistent waves where that is at most one a SIMD (mx_grid).
+double mx_ns(int k, int64_t blocks, int64_t simds, int per_cu) {
+  const int64_t slots = per_cu * simds / 4;
+  const int64_t tiles = (blocks + mx_blocks(k, false) - 1) / mx_blocks(k, false);
+  const double wave = k == 6 ? 106.0 : k == 7 ? 95.0 : 115.0;
+  if (per_cu <= 4) return (double)((tiles + slots - 1) / slots) * wave;
+  const double share = tiles > simds ? 1.55 * wave : tiles > simds / 2 ? 1.3 * wave : wave;
+  return tiles > slots ? (double)tiles / (double)slots * share : share;
+}
+// 4 registers: each further wave on a SIMD 16 more, as many as fit at a time.
+double quad_ns(int k, int64_t blocks, int64_t simds, int per_cu) {
+  const double lone = k == 3 ? 66.0 : k == 4 ? 54.0 : 44.0;
+  const double waves = (double)((blocks + mx_blocks(k, true) - 1) / mx_blocks(k, true)) / (double)simds;
+  const double fit = per_cu > 4 ? per_cu / 4.0 : 1.0;
+  if (per_cu < 4) return lone * (waves * 4 / per_cu > 1 ? waves * 4 / per_cu : 1);
+  if (waves <= 1) return lone;
+  return waves <= fit ? lone + 16 * (waves - 1) : waves / fit * (lone + 16 * (fit - 1));
+}
+
+enum IntKernel { kOneBlock, kMx, kQuad };
+// lds_mx, lds_quad: LDS bytes of a wave, or 0 where the layout cannot run.
+IntKernel fastest(int k, int64_t blocks, int64_t lds_mx, int64_t lds_quad, int num_cu, int max_lds) {
+  const int64_t simds = 4 * (int64_t)num_cu;
+  IntKernel best = kOneBlock;
+  double ns = one_block_ns(k, blocks, simds);
+  for (const IntKernel one : {kMx, kQuad}) {
+    const int64_t lds = one == kQuad ? lds_quad : lds_mx;
+    const int per_cu = lds ? mx_waves_per_cu(lds, max_lds, one == kQuad) : 0;
+    if (per_cu < 1) continue;
+    const double t = one == kQuad ? quad_ns(k, blocks, simds, per_cu) : mx_ns(k, blocks, simds, per_cu);
+    if (t < ns) {
+      ns = t;
+      best = one;
+    }
+  }
+  return best;
 }
 
 // Workgroups (of one wave): one per tile, refilled by the dispatcher, where
-// two waves share a SIMD; where LDS allows at most one per SIMD, that many
-// persistent waves (K=7, L = 512, 2^24 bits: 117 us against 149, the
-// dispatcher's refills landing two on one SIMD).
-unsigned mx_grid(int k, int64_t blocks, int64_t lds, int num_cu, int max_lds) {
-  const int64_t tiles = (blocks + mx_blocks(k) - 1) / mx_blocks(k);
-  const int per_cu = mx_waves_per_cu(lds, max_lds);
+// several waves share a SIMD; where LDS allows at most one per SIMD, that many
+// persistent waves (K=7, L = 512, 2^24 bits, 16 registers: 117 us against 149,
+// the dispatcher's refills landing two on one SIMD).
+unsigned mx_grid(int k, int64_t blocks, int64_t lds, int num_cu, int max_lds, bool quad) {
+  const int64_t tiles = (blocks + mx_blocks(k, quad) - 1) / mx_blocks(k, quad);
+  const int per_cu = mx_waves_per_cu(lds, max_lds, quad);
   const int64_t slots = (int64_t)per_cu * num_cu;
   return (unsigned)(per_cu <= 4 && tiles > slots ? slots : tiles);
 }
 
-hipError_t launch_blocked_mx(const DecodeArgs &a, int64_t lds, hipStream_t stream) {
-  void *fn = pick_kernel_mx(a.k, a.beta, a.llr_type, false);
+hipError_t launch_blocked_mx(const DecodeArgs &a, int64_t lds, bool quad, hipStream_t stream) {
+  void *fn = pick_kernel_mx(a.k, a.beta, a.llr_type, false, quad);
   if (lds > 65536) {
     const hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (err != hipSuccess) return err;
   }
   DecodeArgs args = a;
   void *kargs[] = {&args};
-  const hipError_t err = hipLaunchKernel(fn, dim3(mx_grid(a.k, a.nblocks, lds, t_dev.num_cu, t_dev.max_lds)), dim3(64), kargs, (size_t)lds, stream);
+  const unsigned grid = mx_grid(a.k, a.nblocks, lds, t_dev.num_cu, t_dev.max_lds, quad);
+  const hipError_t err = hipLaunchKernel(fn, dim3(grid), dim3(64), kargs, (size_t)lds, stream);
   if (err != hipSuccess) return err;
   return hipGetLastError();
 }
@@ -274,9 +318,12 @@ hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsuppor
       return hipSuccess;
     }
     if (m == kMetric16) return launch_blocked16(a, stream, unsupported, why);
-    if (a.k >= 5 && a.nblocks > 1) {
-      const int64_t lds = mx_lds_bytes(a.k, a.L + a.v2);
-      if (lds <= t_dev.max_lds && mx_is_faster(a.k, a.nblocks, lds, t_dev.num_cu, t_dev.max_lds)) return launch_blocked_mx(a, lds, stream);
+    if (a.nblocks > 1) {
+      const int64_t traced = a.L + a.v2;
+      const int64_t mx = mx_takes(a.k, false) ? mx_lds_bytes(a.k, traced, false) : 0;
+      const int64_t quad = mx_takes(a.k, true) ? mx_lds_bytes(a.k, traced, true) : 0;
+      const IntKernel which = fastest(a.k, a.nblocks, mx, quad, t_dev.num_cu, t_dev.max_lds);
+      if (which != kOneBlock) return launch_blocked_mx(a, which == kQuad ? quad : mx, which == kQuad, stream);
     }
   } else if (a.llr_type != VIT_LLR_F32) {
     // subframe traceback: the exact-in-fp32 integer kernels only
@@ -356,9 +403,13 @@ unsigned batch_launch_grid(const BatchLaunch &bl, int64_t count, int64_t max_blo
 }
 
 BatchGrid batch_grid_for(const BatchLaunch &bl, int64_t count, int64_t max_block_stages, bool whole_words) {
-  const int64_t lds = (int64_t)bl.mx_lds;
-  if (bl.mx_fn && whole_words && mx_is_faster(bl.k, count, lds, bl.num_cu, bl.max_lds))
-    return {bl.mx_fn, mx_grid(bl.k, count, lds, bl.num_cu, bl.max_lds), 64, bl.mx_lds};
+  if (whole_words) {
+    const IntKernel which =
+        fastest(bl.k, count, (int64_t)bl.mx_lds[0], (int64_t)bl.mx_lds[1], bl.num_cu, bl.max_lds);
+    const bool quad = which == kQuad;
+    if (which != kOneBlock)
+      return {bl.mx_fn[quad], mx_grid(bl.k, count, (int64_t)bl.mx_lds[quad], bl.num_cu, bl.max_lds, quad), 64, bl.mx_lds[quad]};
+  }
   return {bl.fn, batch_launch_grid(bl, count, max_block_stages, bl.num_cu), bl.block, bl.lds};
 }
 
@@ -372,8 +423,10 @@ hipError_t plan_batch_launch(int k, int beta, const uint32_t *gen, int in, int m
   bl->k = k;
   bl->num_cu = t_dev.num_cu;
   bl->max_lds = t_dev.max_lds;
-  bl->mx_fn = nullptr;
-  bl->mx_lds = 0;
+  for (const bool quad : {false, true}) {
+    bl->mx_fn[quad] = nullptr;
+    bl->mx_lds[quad] = 0;
+  }
   const int metric = resolve_metric(k, beta, in, metric_bits, max_block_stages, why);
   if (metric < 0) {
     *unsupported = 1;
@@ -452,11 +505,14 @@ hipError_t plan_batch_launch(int k, int beta, const uint32_t *gen, int in, int m
   bl->lds_words_per_wave = (int)(lds_wave / 4);
   bl->items_per_wave = 1;
   bl->metric_bits = metric;
-  if (in != VIT_LLR_F32 && k >= 5 && traced > 0 && mx_lds_bytes(k, traced) <= t_dev.max_lds) {
-    bl->mx_fn = pick_kernel_mx(k, beta, in, true);
-    bl->mx_lds = (size_t)mx_lds_bytes(k, traced);
-    if (bl->mx_lds > 65536) {
-      err = hipFuncSetAttribute(bl->mx_fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bl->mx_lds);
+  for (const bool quad : {false, true}) {
+    if (in == VIT_LLR_F32 || traced <= 0 || !mx_takes(k, quad)) continue;
+    const int64_t need = mx_lds_bytes(k, traced, quad);
+    if (need > t_dev.max_lds) continue;
+    bl->mx_fn[quad] = pick_kernel_mx(k, beta, in, true, quad);
+    bl->mx_lds[quad] = (size_t)need;
+    if (need > 65536) {
+      err = hipFuncSetAttribute(bl->mx_fn[quad], hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
       if (err != hipSuccess) return err;
     }
   }
