@@ -94,20 +94,22 @@ __device__ __forceinline__ int parity32(uint32_t x) { return __builtin_popcount(
 // c = +inf (keep the max) or -inf (keep the min).  The compare mask of this
 // stage is returned in `pend` and shifted into the decision word d by the NEXT
 // stage's block (d = 2d + pend), which keeps every hazard distance >= 2
-// instructions without s_nop:
+// instructions without s_nop (the carry out goes back to the mask's registers:
+// into VCC, which every stage's carry-out would write again, the stage's five
+// instructions took 8.5 ns with the SIMD full and 12.4 for a wave alone, so
+// 7.4 and 11.6; K=7 r1/2, 2^24 bits, L = 512: 239 us, so 227):
 //   * the DPP read of o comes 2 VALU ops after the previous stage's med3 wrote it;
 //   * the VALU-written compare mask is read as a carry 2 VALU ops after.
 // Instruction order: B = s*o - x; d += prev mask; A = s*o(partner) + x;
 // mask = A > B; o = med3(A, B, c).
 #define VIT_ACS_DPP(DPPSTR, SN, BTERM)                                                   \
   asm volatile("v_fma_f32 %[B], " SN "%[s], %[o], " BTERM "\n\t"                         \
-               "v_addc_co_u32 %[d], vcc, %[d], %[d], %[pd]\n\t"                          \
+               "v_addc_co_u32 %[d], %[pd], %[d], %[d], %[pd]\n\t"                          \
                "v_fmac_f32_dpp %[x], %[o], " SN "%[s] " DPPSTR "\n\t"                    \
                "v_cmp_gt_f32 %[pd], %[x], %[B]\n\t"                                      \
                "v_med3_f32 %[o], %[x], %[B], %[c]"                                       \
                : [o] "+v"(o), [x] "+v"(x), [d] "+v"(d), [B] "=&v"(B), [pd] "+s"(pend)    \
-               : [s] "v"(s), [c] "v"(c), [y] "v"(y)                                      \
-               : "vcc")
+               : [s] "v"(s), [c] "v"(c), [y] "v"(y))
 
 // Slot bits 4 and 5 flip lane bits 4 and 5 (xor 16 / xor 32): the partner
 // metric comes from v_permlane16_swap / v_permlane32_swap of o with itself,
@@ -115,23 +117,22 @@ __device__ __forceinline__ int parity32(uint32_t x) { return __builtin_popcount(
 // dead after B, and rewritten by med3).  Same hazard distances as the DPP form.
 #define VIT_ACS_PERM(PERM, SN, BTERM)                                                    \
   asm volatile("v_fma_f32 %[B], " SN "%[s], %[o], " BTERM "\n\t"                         \
-               "v_addc_co_u32 %[d], vcc, %[d], %[d], %[pd]\n\t"                          \
+               "v_addc_co_u32 %[d], %[pd], %[d], %[d], %[pd]\n\t"                          \
                PERM " %[o], %[o]\n\t"                                                    \
                "v_fma_f32 %[x], " SN "%[s], %[o], %[x]\n\t"                              \
                "v_cmp_gt_f32 %[pd], %[x], %[B]\n\t"                                      \
                "v_med3_f32 %[o], %[x], %[B], %[c]"                                       \
                : [o] "+v"(o), [x] "+v"(x), [d] "+v"(d), [B] "=&v"(B), [pd] "+s"(pend)    \
-               : [s] "v"(s), [c] "v"(c), [y] "v"(y)                                      \
-               : "vcc")
+               : [s] "v"(s), [c] "v"(c), [y] "v"(y))
 
 // Both predecessors in the same lane (slot bit q >= 6 is a register bit):
 // registers a (own predecessor even) and b (odd).
 #define VIT_ACS_PAIR(SA, SB, BTA, BTB)                                                   \
   asm volatile("v_fma_f32 %[Ba], " SA "%[s], %[oa], " BTA "\n\t"                         \
-               "v_addc_co_u32 %[da], vcc, %[da], %[da], %[pa]\n\t"                       \
+               "v_addc_co_u32 %[da], %[pa], %[da], %[da], %[pa]\n\t"                       \
                "v_fma_f32 %[xa], " SA "%[s], %[ob], %[xa]\n\t"                           \
                "v_fma_f32 %[Bb], " SB "%[s], %[ob], " BTB "\n\t"                         \
-               "v_addc_co_u32 %[db], vcc, %[db], %[db], %[pb]\n\t"                       \
+               "v_addc_co_u32 %[db], %[pb], %[db], %[db], %[pb]\n\t"                       \
                "v_fma_f32 %[xb], " SB "%[s], %[oa], %[xb]\n\t"                           \
                "v_cmp_gt_f32 %[pa], %[xa], %[Ba]\n\t"                                    \
                "v_med3_f32 %[oa], %[xa], %[Ba], %[ca]\n\t"                               \
@@ -140,16 +141,13 @@ __device__ __forceinline__ int parity32(uint32_t x) { return __builtin_popcount(
                : [oa] "+v"(oa), [ob] "+v"(ob), [xa] "+v"(xa), [xb] "+v"(xb),             \
                  [da] "+v"(da), [db] "+v"(db), [Ba] "=&v"(Ba), [Bb] "=&v"(Bb),           \
                  [pa] "+s"(pa), [pb] "+s"(pb)                                            \
-               : [s] "v"(s), [ca] "v"(ca), [cb] "v"(cb), [ya] "v"(ya), [yb] "v"(yb)      \
-               : "vcc")
+               : [s] "v"(s), [ca] "v"(ca), [cb] "v"(cb), [ya] "v"(ya), [yb] "v"(yb))
 
 // Shift the last pending decision mask into the word (end of a body).
 __device__ __forceinline__ void flush_decision(uint32_t &d, uint64_t &pend) {
   asm volatile("s_nop 1\n\t"
-               "v_addc_co_u32 %[d], vcc, %[d], %[d], %[pd]"
-               : [d] "+v"(d)
-               : [pd] "s"(pend)
-               : "vcc");
+               "v_addc_co_u32 %[d], %[pd], %[d], %[d], %[pd]"
+               : [d] "+v"(d), [pd] "+s"(pend));
   pend = 0;
 }
 
