@@ -31,9 +31,10 @@
 //    each stage every slot fetches its own one with ds_bpermute (LDS crossbar,
 //    no VALU).  The complement identity (eq. 8) gives the partner branch as a
 //    negation, folded into the fma.
-//  * Decisions: 32 stages per dword per lane, stored to LDS.  Traceback runs
-//    on the scalar unit: one v_readlane per stage; the lane to read moves by
-//    replacing one bit of the slot index with the decision bit.
+//  * Decisions: 32 stages per dword per lane, stored to LDS.  The traceback
+//    composes a body's decisions per period, for all slots and periods at once
+//    (a few vector operations per phase), and then takes one v_readlane per
+//    period of k-1 stages.
 //  * The unrolled loop body covers lcm(k-1, tile, 32) stages; a block enters it
 //    at an offset (Duff's device) chosen so that its last stage is the body's
 //    last, which makes the final state of slot j equal to j.
@@ -575,57 +576,69 @@ struct Decoder {
   // (BODY is a multiple of P, so the rotation there is the identity).
   __device__ __forceinline__ int best_state() const { return best_slot_after<BODY - 1>(); }
 
-  // Traceback (Algorithm 2) through one group (body) of survivor words for
-  // each of NCH independent chains, interleaved so that the scalar steps of
-  // one chain fill the latency of the other's.  ulam[c] is chain c's slot
-  // index (the current state).  Following the survivor at body offset pos
-  // replaces bit q = pos mod P of the slot index with the decision bit; the
-  // survivor words hold that bit XOR the slot's own bit q, so the step is
-  // ulam ^= (word bit) << q.  The words are bit-reversed and, per phase
-  // period p0..p0+P-1, shifted so that offset p0 + q sits at bit q: a step is
-  // one v_readlane and two scalar operations.  After a period the slot index
-  // holds that period's P decision bits; the group's decision word replaces
-  // its first survivor word in LDS when wr[c] (every lane writes the same
-  // word).
-  template <int NCH>
-  __device__ __forceinline__ void tb_groups(const int (&grp)[NCH], uint32_t (&ulam)[NCH],
-                                            const bool (&wr)[NCH]) const {
-    uint32_t dv[NCH][REGS];
+  // v of lane ^ 1 << Q.
+  template <int Q>
+  __device__ __forceinline__ static uint32_t across(uint32_t v) {
+    if constexpr (Q == 0) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);        // quad_perm [1,0,3,2]
+    else if constexpr (Q == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+    else if constexpr (Q == 2)  // row_half_mirror, then quad_perm [3,2,1,0]: lane xor 7 and 3
+      return (uint32_t)__builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
+    else if constexpr (Q == 3) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true);  // row_ror:8
+    else {
+      if constexpr (Q == 4) asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %0" : "+v"(v));
+      else asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %0" : "+v"(v));
+      return v;
+    }
+  }
+
+  // Of a body's words (bit g: whether following the survivor at offset g flips
+  // bit g mod P of the slot index), each period's P bits put together: what
+  // they are for a survivor that leaves the period in this slot.  Phase by
+  // phase, the bits below q are the other slot's where bit q flips; all periods
+  // of the body at once.
+  template <int Q>
+  __device__ __forceinline__ static void compose(uint32_t (&w)[REGS]) {
+    if constexpr (Q < P) {
+      constexpr uint32_t kBit = [] {  // bit Q of every period
+        uint32_t m = 0;
+        for (int a = 0; a < BODY; a += P) m |= 1u << (a + Q);
+        return m;
+      }();
+      uint32_t below[REGS], other[REGS];
 #pragma unroll
-    for (int c = 0; c < NCH; ++c)
+      for (int r = 0; r < REGS; ++r) {
+        const uint32_t flip = w[r] & kBit;
+        below[r] = flip - (flip >> Q);
+        if constexpr (Q < 6) other[r] = across<Q>(w[r]);
+        else other[r] = w[r ^ (Q < 6 ? 0 : 1 << (Q - 6))];
+      }
 #pragma unroll
-      for (int rr = 0; rr < REGS; ++rr) dv[c][rr] = __builtin_bitreverse32(lds[(grp[c] * REGS + rr) * 64 + lane]);
-    uint32_t acc[NCH];
+      for (int r = 0; r < REGS; ++r) w[r] = (other[r] & below[r]) | (w[r] & ~below[r]);
+      compose<Q + 1>(w);
+    }
+  }
+
+  // Traceback (Algorithm 2) through one group (body) of survivor words, which
+  // hold the decisions XOR the slot's own bit: the words of all slots are
+  // composed per period, and a period of the chain is one v_readlane (a stage at
+  // a time that was P, each with two scalar operations behind it: K=7 r1/2,
+  // 4096 bits, L = 256 14.6 us, so 11.7; 2^24 bits, L = 512 227, so 211).  After
+  // a period the slot index holds its P decision bits; the group's decision word replaces its first survivor word in
+  // LDS (every lane writes the same word).
+  __device__ __forceinline__ void tb_group(int grp, uint32_t &ulam) const {
+    uint32_t w[REGS];
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) acc[c] = 0;
+    for (int r = 0; r < REGS; ++r) w[r] = __builtin_bitreverse32(lds[(grp * REGS + r) * 64 + lane]) >> (32 - BODY);
+    compose<1>(w);
+    uint32_t acc = 0;
 #pragma unroll
     for (int p0 = BODY - P; p0 >= 0; p0 -= P) {
-      uint32_t sh[NCH][REGS], src[NCH];
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-#pragma unroll
-        for (int rr = 0; rr < REGS; ++rr) sh[c][rr] = dv[c][rr] >> (32 - BODY + p0);
-        src[c] = sh[c][0];
-      }
-#pragma unroll
-      for (int q = P - 1; q >= 0; --q) {
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-          if constexpr (REGS > 1) {
-            // the register holding slot ulam is given by bits >= 6 of the
-            // slot index, which change only at q >= 6: select at q >= 5 only
-            if (q >= 5) src[c] = select_reg<REGS>(sh[c], ulam[c] >> 6);
-          }
-          const uint32_t w = __builtin_amdgcn_readlane(src[c], (int)(ulam[c] & 63u));
-          ulam[c] ^= w & (1u << q);
-        }
-      }
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) acc[c] |= (ulam[c] & (uint32_t)(S - 1)) << p0;
+      uint32_t src = w[0];
+      if constexpr (REGS > 1) src = select_reg<REGS>(w, ulam >> 6);
+      ulam ^= (__builtin_amdgcn_readlane(src, (int)(ulam & 63u)) >> p0) & (uint32_t)(S - 1);
+      acc |= ulam << p0;
     }
-#pragma unroll
-    for (int c = 0; c < NCH; ++c)
-      if (wr[c]) lds[(grp[c] * REGS) * 64] = acc[c];
+    lds[(grp * REGS) * 64] = acc;
   }
 
   template <int Q>
@@ -875,24 +888,20 @@ __device__ __forceinline__ void decode_block(Decoder<K, BETA, STD, IN> &D, const
     return;
   }
 
-  // ---- traceback on the scalar unit (Decoder::tb_groups).  The decision bit
-  // at offset g is the input bit of offset g - (k-1) (the oldest input of the
-  // state), so the decision stream, followed by the k-1 bits of the upper
+  // ---- traceback (Decoder::tb_group).  The decision bit at offset g is the
+  // input bit of offset g - (k-1) (the oldest input of the state), so the
+  // decision stream, followed by the k-1 bits of the upper
   // chain's start slot, is the decoded sequence shifted by k-1: bit t of the
   // output is stream bit (t - stage_base) + k - 1.
-  // The traceback is a short serial chain of scalar steps: raise the wave's
+  // The traceback is a short serial chain: raise the wave's
   // issue priority while it runs so that waves in their forward pass do not
   // stretch it (measured: about 8% faster overall).
   const int grp_lo = ((int)(cs - s) + r) / BODY;
   __builtin_amdgcn_s_setprio(1);
   const uint32_t lam_start = (uint32_t)lam;
   {
-    uint32_t u1[1] = {(uint32_t)lam};
-    const bool w1[1] = {true};
-    for (int grp = nbody - 1; grp >= grp_lo; --grp) {
-      const int g1[1] = {grp};
-      D.template tb_groups<1>(g1, u1, w1);
-    }
+    uint32_t u = (uint32_t)lam;
+    for (int grp = nbody - 1; grp >= grp_lo; --grp) D.tb_group(grp, u);
   }
   __builtin_amdgcn_s_setprio(0);
 
