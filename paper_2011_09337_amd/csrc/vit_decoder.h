@@ -618,6 +618,12 @@ struct Decoder {
     }
   }
 
+  __device__ __forceinline__ void composed(int grp, uint32_t (&w)[REGS]) const {
+#pragma unroll
+    for (int r = 0; r < REGS; ++r) w[r] = __builtin_bitreverse32(lds[(grp * REGS + r) * 64 + lane]) >> (32 - BODY);
+    compose<1>(w);
+  }
+
   // Traceback (Algorithm 2) through one group (body) of survivor words, which
   // hold the decisions XOR the slot's own bit: the words of all slots are
   // composed per period, and a period of the chain is one v_readlane (a stage at
@@ -627,9 +633,7 @@ struct Decoder {
   // LDS (every lane writes the same word).
   __device__ __forceinline__ void tb_group(int grp, uint32_t &ulam) const {
     uint32_t w[REGS];
-#pragma unroll
-    for (int r = 0; r < REGS; ++r) w[r] = __builtin_bitreverse32(lds[(grp * REGS + r) * 64 + lane]) >> (32 - BODY);
-    compose<1>(w);
+    composed(grp, w);
     uint32_t acc = 0;
 #pragma unroll
     for (int p0 = BODY - P; p0 >= 0; p0 -= P) {
@@ -826,20 +830,23 @@ __device__ __forceinline__ void decode_block(Decoder<K, BETA, STD, IN> &D, const
     // body offset pos (q = pos mod P) the decoded bit of stage t is bit q of
     // u (the state's newest input, rotated into place) and following the
     // survivor flips bit q by the stored word bit (decision XOR own bit q).
-    // Decoded bits go to one LDS byte each, after the survivors.
+    // The stages down to a period's end are taken one by one; then the words
+    // are composed (see compose) and a chain takes a period at a time, whose
+    // decoded bits are those of its slot (a stage at a time throughout:
+    // K=7 r1/2, 2^22 bits, L = 512, f0 = 56, w = 45 83.1 us, so 76.2).  Decoded bits go to
+    // one LDS byte each, after the survivors.
     uint8_t *dbytes = (uint8_t *)(D.lds + nbody * REGS * 64);
     const int c = D.lane;
-    int len = 0, t = 0, b_end = 0, pos = 0, q = 0, bdy = 0;
+    int t = 0, a_lo = 1, b_end = 0, pos = P - 1, bdy = 0;
     uint32_t u = 0;
     if (c < C) {
-      const int a_lo = (int)cs + c * f0;
+      a_lo = (int)cs + c * f0;
       b_end = a_lo + f0 < (int)ce ? a_lo + f0 : (int)ce;
       const bool inner = c < n_inner;
       const int x = inner ? b_end + sa.w : (int)e;
       const int rel = x - 1 - (int)D.stage_base;
       bdy = rel / BODY;
       pos = rel - bdy * BODY;
-      q = pos % P;
       if (!inner) {
         u = (uint32_t)lam;  // the block end is a body end: slot j holds state j
       } else if (sa.start == VIT_SUBFRAME_RANDOM) {
@@ -850,23 +857,43 @@ __device__ __forceinline__ void decode_block(Decoder<K, BETA, STD, IN> &D, const
         u = snap_v;
       }
       t = x - 1;
-      len = x - a_lo;
     }
-    int maxlen = len;
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-      const int o = __shfl_xor(maxlen, m);
-      maxlen = o > maxlen ? o : maxlen;
-    }
-    maxlen = __builtin_amdgcn_readfirstlane(maxlen);
-    for (int i = 0; i < maxlen; ++i) {
-      if (i < len) {
+    auto word = [&]() -> uint32_t { return D.lds[(bdy * REGS + (int)(u >> 6)) * 64 + (int)(u & 63u)]; };
+    for (int q = pos % P; __builtin_amdgcn_ballot_w64(t >= a_lo && q != P - 1);) {
+      if (t >= a_lo && q != P - 1) {
         if (t < b_end) dbytes[t - (int)cs] = (uint8_t)((u >> q) & 1u);
-        const uint32_t wd = D.lds[(bdy * REGS + (int)(u >> 6)) * 64 + (int)(u & 63u)];
-        u ^= ((wd >> (BODY - 1 - pos)) & 1u) << q;
-        --t;
+        u ^= ((word() >> (BODY - 1 - pos)) & 1u) << q;
         q = q == 0 ? P - 1 : q - 1;
+        --t;
         if (--pos < 0) {
+          pos = BODY - 1;
+          --bdy;
+        }
+      }
+    }
+    auto lds_phase = [] {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    lds_phase();
+    for (int grp = ((int)(cs - s) + r) / BODY; grp < nbody; ++grp) {
+      uint32_t w[REGS];
+      D.composed(grp, w);
+#pragma unroll
+      for (int rr = 0; rr < REGS; ++rr) D.lds[(grp * REGS + rr) * 64 + D.lane] = w[rr];
+    }
+    lds_phase();
+    while (__builtin_amdgcn_ballot_w64(t >= a_lo)) {
+      if (t >= a_lo) {
+        const uint32_t flips = (word() >> (pos - (P - 1))) & (uint32_t)(S - 1);
+#pragma unroll
+        for (int q = P - 1; q >= 0; --q, --t) {
+          if (t < b_end && t >= a_lo) dbytes[t - (int)cs] = (uint8_t)((u >> q) & 1u);
+        }
+        u ^= flips;
+        pos -= P;
+        if (pos < 0) {
           pos = BODY - 1;
           --bdy;
         }
@@ -874,9 +901,7 @@ __device__ __forceinline__ void decode_block(Decoder<K, BETA, STD, IN> &D, const
     }
     // ---- output: lane-parallel packing of the decoded bytes (the wave's
     // LDS writes are complete before its reads).
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    lds_phase();
     const int64_t b_lo = cs >> 3, b_hi = (ce - 1) >> 3;
     for (int64_t B = b_lo + D.lane; B <= b_hi; B += 64) {
       const int base = (int)(8 * B - cs);
