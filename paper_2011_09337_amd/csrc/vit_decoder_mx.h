@@ -553,88 +553,26 @@ __device__ __forceinline__ void first_loads(D &d, int r) {
   }
 }
 
-// Decode NB blocks; lane tau < NB describes block tau (lanes above: any block
-// again).  The caller guarantees windows of at least P stages that lie in
-// memory from `before` bytes ahead on.
-// `describe` is called before the recursion and again after it, which costs
-// less than holding its result in registers.
-template <int K, int BETA, int IN, bool QUAD, class Describe>
-__device__ __forceinline__ void decode_tile(DecoderM<K, BETA, IN, QUAD> &D, Describe describe) {
-  Blk bk = describe();
-  using Sh = ShapeM<K, BETA, QUAD>;
-  constexpr int P = Sh::P, S = Sh::S, NB = Sh::NB, NCLS = Sh::NCLS, NG = Sh::NG, BODY = Sh::BODY, R = Sh::R;
-  const int lane = D.lane;
-  const int most = wave_max_all(bk.M);
-  const int r = (BODY - most % BODY) % BODY;
-  const int nbody = (most + r) / BODY;
-  const int begin = nbody * BODY - bk.M;
-  D.start = 2 * begin + (bk.known ? 1 : 0);
-  const int grp_lo = -wave_max_all(-(begin + bk.core)) / BODY;  // the first body with a core bit's decision
-  D.keep = grp_lo;
-  const int kept = nbody - grp_lo;
-  D.decoded = (kept - Sh::NR > 1 ? kept - Sh::NR : 1) * Sh::REGION;
-  {
-    const int from = D.tau_a(lane) << 2;
-    const uint64_t p = (uint64_t)bk.llr;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)p);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(p >> 32));
-    D.llr = (gin_t)(((uint64_t)hi << 32) | lo);
-    const int M = __builtin_amdgcn_ds_bpermute(from, bk.M);
-    D.off0 = (M - nbody * BODY + D.dword_of(lane) * Sh::SPD) * BETA - (BETA == 3 ? 1 : 0);
-    D.before = -__builtin_amdgcn_ds_bpermute(from, bk.before);
-    D.end = M * BETA - 4;
-  }
-#pragma unroll
-  for (int x = 0; x < R; ++x) {
-    D.o[x] = D.kZero + D.own_tag(x);
-    D.dec[x] = 0u;
-  }
-  D.body = 0;
-  first_loads<0>(D, r);
-  const int starts_in = begin / BODY;
-  while (D.body < nbody) {  // one body in which blocks start (as in the first), and those up to the next such
-    const int from = D.body == 0 ? r : 0;
-    VITM_X32(VITM_G1, BODY)
-    for (++D.body; D.body < nbody && !__builtin_amdgcn_ballot_w64(starts_in == D.body); ++D.body) {
-      VITM_X32(VITM_U1, BODY)
-    }
-  }
-  lds_phase();
-  bk = describe();
+// From the survivors to the decoded bytes: uc is lane tau's block's best state's
+// complement.
+template <class D_>
+__device__ __forceinline__ void trace_tile(D_ &D, const Blk &bk, uint32_t uc, int nbody, int grp_lo) {
+  using Sh = typename D_::Sh;
+  constexpr int P = Sh::P, S = Sh::S, NB = Sh::NB, NG = Sh::NG, BODY = Sh::BODY, R = Sh::R;
+  const int lane = D.lane, kept = nbody - grp_lo;
   const int gcore = nbody * BODY - bk.M + bk.core;
-
-  // ---- traceback starts: block tau's best state (largest metric, largest
-  // complement) to lane tau
-  uint32_t uc = S - 1;
-#pragma unroll
-  for (int c = 0; c < NCLS; ++c) {
-    int m = INT32_MIN;
-#pragma unroll
-    for (int x = 0; x < R; ++x)
-      if (D.reg_class(x) == c) m = max_i(m, D.o[x]);
-    m = max_i(m, devi::exchange<0>(m));
-    m = max_i(m, devi::exchange<1>(m));
-    if constexpr (P > 2) m = max_i(m, devi::exchange<2>(m));
-    if constexpr (P > 3) m = max_i(m, devi::exchange<3>(m));
-    if constexpr (QUAD && P > 4) m = max_i(m, devi::exchange<4>(m));
-    if constexpr (QUAD && P > 5) m = max_i(m, devi::exchange<5>(m));
-    // to lane tau, if class c is its block's: any lane that holds the block
-    constexpr int kQ = 2 - Sh::IB;  // bits of tau below the row quad
-    const int at = QUAD ? ((lane >> 2) << P) & 63 : ((lane >> kQ) & 3) << 4;
-    const int got = __builtin_amdgcn_ds_bpermute(at << 2, m);
-    const int mine = QUAD ? lane & 3 : ((lane >> (kQ + 2)) << kQ) | (lane & ((1 << kQ) - 1));
-    uc = mine == c ? (uint32_t)got & (uint32_t)(S - 1) : uc;
-  }
   if (bk.zero) uc = S - 1;
   const uint32_t lam_start = uc ^ (uint32_t)(S - 1);
   for (int grp = kept - 1; grp >= 0; --grp) {
     int region = grp - Sh::NR;
-    if (region < 0) {
-      region = 0;
-      uint32_t d[R];
-      kept_words(grp, d);
-      D.store_words(0, d);
-      lds_phase();
+    if constexpr (Sh::NR > 0) {
+      if (region < 0) {
+        region = 0;
+        uint32_t d[R];
+        kept_words(grp, d);
+        D.store_words(0, d);
+        lds_phase();
+      }
     }
     if (lane < NB) {
       const uint32_t *w = D.lds + region * Sh::REGION;
@@ -684,6 +622,80 @@ __device__ __forceinline__ void decode_tile(DecoderM<K, BETA, IN, QUAD> &D, Desc
     }
   }
   lds_phase();
+}
+
+// Decode NB blocks; lane tau < NB describes block tau (lanes above: any block
+// again).  The caller guarantees windows of at least P stages that lie in
+// memory from `before` bytes ahead on.
+// `describe` is called before the recursion and again after it, which costs
+// less than holding its result in registers.
+template <int K, int BETA, int IN, bool QUAD, class Describe>
+__device__ __forceinline__ void decode_tile(DecoderM<K, BETA, IN, QUAD> &D, Describe describe) {
+  Blk bk = describe();
+  using Sh = ShapeM<K, BETA, QUAD>;
+  constexpr int P = Sh::P, S = Sh::S, NCLS = Sh::NCLS, BODY = Sh::BODY, R = Sh::R;
+  const int lane = D.lane;
+  const int most = wave_max_all(bk.M);
+  const int r = (BODY - most % BODY) % BODY;
+  const int nbody = (most + r) / BODY;
+  const int begin = nbody * BODY - bk.M;
+  D.start = 2 * begin + (bk.known ? 1 : 0);
+  const int grp_lo = -wave_max_all(-(begin + bk.core)) / BODY;  // the first body with a core bit's decision
+  D.keep = grp_lo;
+  const int kept = nbody - grp_lo;
+  D.decoded = (kept - Sh::NR > 1 ? kept - Sh::NR : 1) * Sh::REGION;
+  {
+    const int from = D.tau_a(lane) << 2;
+    const uint64_t p = (uint64_t)bk.llr;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)p);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(p >> 32));
+    D.llr = (gin_t)(((uint64_t)hi << 32) | lo);
+    const int M = __builtin_amdgcn_ds_bpermute(from, bk.M);
+    D.off0 = (M - nbody * BODY + D.dword_of(lane) * Sh::SPD) * BETA - (BETA == 3 ? 1 : 0);
+    D.before = -__builtin_amdgcn_ds_bpermute(from, bk.before);
+    D.end = M * BETA - 4;
+  }
+#pragma unroll
+  for (int x = 0; x < R; ++x) {
+    D.o[x] = D.kZero + D.own_tag(x);
+    D.dec[x] = 0u;
+  }
+  D.body = 0;
+  first_loads<0>(D, r);
+  const int starts_in = begin / BODY;
+  while (D.body < nbody) {  // one body in which blocks start (as in the first), and those up to the next such
+    const int from = D.body == 0 ? r : 0;
+    VITM_X32(VITM_G1, BODY)
+    for (++D.body; D.body < nbody && !__builtin_amdgcn_ballot_w64(starts_in == D.body); ++D.body) {
+      VITM_X32(VITM_U1, BODY)
+    }
+  }
+  lds_phase();
+  bk = describe();
+
+  // ---- traceback starts: block tau's best state (largest metric, largest
+  // complement) to lane tau
+  uint32_t uc = S - 1;
+#pragma unroll
+  for (int c = 0; c < NCLS; ++c) {
+    int m = INT32_MIN;
+#pragma unroll
+    for (int x = 0; x < R; ++x)
+      if (D.reg_class(x) == c) m = max_i(m, D.o[x]);
+    m = max_i(m, devi::exchange<0>(m));
+    m = max_i(m, devi::exchange<1>(m));
+    if constexpr (P > 2) m = max_i(m, devi::exchange<2>(m));
+    if constexpr (P > 3) m = max_i(m, devi::exchange<3>(m));
+    if constexpr (QUAD && P > 4) m = max_i(m, devi::exchange<4>(m));
+    if constexpr (QUAD && P > 5) m = max_i(m, devi::exchange<5>(m));
+    // to lane tau, if class c is its block's: any lane that holds the block
+    constexpr int kQ = 2 - Sh::IB;  // bits of tau below the row quad
+    const int at = QUAD ? ((lane >> 2) << P) & 63 : ((lane >> kQ) & 3) << 4;
+    const int got = __builtin_amdgcn_ds_bpermute(at << 2, m);
+    const int mine = QUAD ? lane & 3 : ((lane >> (kQ + 2)) << kQ) | (lane & ((1 << kQ) - 1));
+    uc = mine == c ? (uint32_t)got & (uint32_t)(S - 1) : uc;
+  }
+  trace_tile(D, bk, uc, nbody, grp_lo);
 }
 
 // Stream kernel: wave w decodes blocks [NB w, NB w + NB), then those NB x
@@ -779,11 +791,6 @@ VITM_NARROW vit_batch_quad_kernel(BatchArgs a) {
   asm volatile("" ::: "v127");
   batch_mx<K, BETA, IN, true>(a);
 }
-
-#undef VITM_G1
-#undef VITM_U1
-#undef VITM_X8
-#undef VITM_X32
 
 }  // namespace devm
 

@@ -108,9 +108,11 @@ struct BatchLaunch {
   int lds_words_per_wave;
   int items_per_wave;        // work items a wave takes at once (2 for the 16-bit metric kernels)
   int metric_bits;           // 16 or 32 for integer inputs, 0 for FP32
-  int k, num_cu, max_lds;    // the code, and the device it was planned on
+  int k, beta, num_cu, max_lds;  // the code, and the device it was planned on
   const void *mx_fn[2];      // matrix-core kernels for the same blocks (16 and 4 registers), or nullptr
   size_t mx_lds[2];          // their dynamic LDS bytes, or 0
+  const void *row_fn;        // FP32 kernel of four blocks a wave for the same blocks, or nullptr
+  size_t row_lds;            // its dynamic LDS bytes
 };
 // Fill *bl for a code (k, beta, generators, input kind, metric choice as
 // DecodeArgs::metric_bits) decoding blocks of at most max_block_stages

@@ -1,0 +1,6 @@
+// vit_kernels_row_k4.hip -- FP32 kernel instances of four blocks a wave (stream and batch) for constraint length k = 4.
+#include "vit_decoder_row.h"
+
+namespace vit {
+void *pick_kernel_row_k4(int beta, bool batch) { return pick_kernel_row_k<4>(beta, batch); }
+}  // namespace vit

@@ -4,6 +4,7 @@
 #include "vit_decoder16.h"
 #include "vit_decoder_int.h"
 #include "vit_decoder_mx.h"
+#include "vit_decoder_row.h"
 #include "vit_shapes.h"
 
 namespace vit {
@@ -135,6 +136,16 @@ hipError_t device_info() {
 // because they measured faster on gfx950 (the 16-bit kernels hold two
 // blocks' survivors per wave, which halves the waves the LDS admits).
 // -1 = no kernel (why is set).
+void *pick_kernel_row(int k, int beta, bool batch) {
+  switch (k) {
+    case 3: return pick_kernel_row_k3(beta, batch);
+    case 4: return pick_kernel_row_k4(beta, batch);
+    case 5: return pick_kernel_row_k5(beta, batch);
+    case 6: return pick_kernel_row_k6(beta, batch);
+  }
+  return nullptr;
+}
+
 int resolve_metric(int k, int beta, int in, int metric_bits, int64_t max_block_stages, const char **why) {
   if (in == VIT_LLR_F32) return 0;
   const bool fits16 = lds16_bytes_per_wave(k, beta, max_block_stages) <= t_dev.max_lds;
@@ -303,6 +314,54 @@ hipError_t launch_blocked_mx(const DecodeArgs &a, int64_t lds, bool quad, hipStr
   return hipGetLastError();
 }
 
+// ---- the FP32 kernels of four blocks a wave (vit_decoder_row.h)
+
+// (rate 1/4 builds a table per stage and spills: K=4 507 us against 347 at
+// 2^24 bits, L = 64; K=7's four phases across lanes cost what its two permlane
+// phases do: 245 us against 254 at L = 256, and 320 against 238 at L = 512)
+bool row_takes(int k, int beta, const uint32_t *gen) { return k <= 6 && beta <= 3 && taps_both_ends(k, beta, gen); }
+
+// LDS of a wave: the survivors of four blocks, and the decoded words.
+int64_t row_lds_bytes(int k, int64_t traced) {
+  const int64_t body = body_len(k), bodies = (traced + body - 1) / body;
+  return 16 * ((bodies << (k - 1)) + bodies + 1);
+}
+
+// Whether `blocks` FP32 blocks take less time four a wave, by the time per
+// stage (nanoseconds) of both, measured with one wave on a SIMD and with the
+// chip full.  One block a wave: 30, and 10.5 for each further on a SIMD.  Four:
+// 44 (k = 5, rate 1/2), 56 or 62 (k = 6), and 13 (20) for each further wave, as
+// many as registers (four a SIMD) and LDS hold at a time.  Measured (us, one /
+// four a wave): K=5 r1/2, L = 256, 4096 blocks 22 / 18, 16384 63 / 27, 65536
+// 214 / 82; K=5, L = 512, 2048 blocks 23 / 28, 4096 37 / 29; K=6 r1/2, L = 256,
+// 4096 blocks 23 / 25, 8192 36 / 28, 65536 221 / 130; K=6 r1/3, L = 512, 32768
+// blocks 226 / 129; K=3 r1/2, L = 256, 3104 blocks 21 / 21, 65536 204 / 83.
+bool row_is_faster(int k, int beta, int64_t blocks, int64_t lds, int num_cu, int max_lds) {
+  const int64_t unit = (lds + 1279) / 1280 * 1280, by_lds = max_lds / unit;
+  const double fit = by_lds < 16 ? (double)by_lds / 4 : 4.0;
+  if (fit < 0.5) return false;
+  const int64_t simds = 4 * (int64_t)num_cu, tiles = (blocks + 3) / 4;
+  const double one = 30.0 + 10.5 * (double)((blocks - 1) / simds);
+  const double lone = k == 6 ? 62.0 : k == 5 && beta == 2 ? 44.0 : 56.0, more = k == 6 ? 20.0 : 13.0;
+  const double waves = (double)((tiles + simds - 1) / simds);
+  const double four = waves <= fit ? lone + more * (waves - 1) : waves / fit * (lone + more * (fit > 1 ? fit - 1 : 0));
+  return four < one;
+}
+unsigned row_grid(int64_t blocks) { return (unsigned)((blocks + 3) / 4); }
+
+hipError_t launch_blocked_row(const DecodeArgs &a, int64_t lds, hipStream_t stream) {
+  void *fn = pick_kernel_row(a.k, a.beta, false);
+  if (lds > 65536) {
+    const hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (err != hipSuccess) return err;
+  }
+  DecodeArgs args = a;
+  void *kargs[] = {&args};
+  const hipError_t err = hipLaunchKernel(fn, dim3(row_grid(a.nblocks)), dim3(64), kargs, (size_t)lds, stream);
+  if (err != hipSuccess) return err;
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsupported, const char **why) {
@@ -337,6 +396,9 @@ hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsuppor
       *why = "int8 block too long for exact integers in fp32";
       return hipSuccess;
     }
+  } else if (a.sub_bits == 0 && a.nblocks > 1 && row_takes(a.k, a.beta, a.gen)) {
+    const int64_t lds = row_lds_bytes(a.k, a.L + a.v2);
+    if (row_is_faster(a.k, a.beta, a.nblocks, lds, t_dev.num_cu, t_dev.max_lds)) return launch_blocked_row(a, lds, stream);
   }
   const void *fn = a.llr_type != VIT_LLR_F32 && a.sub_bits == 0
                        ? pick_kernel_int(a.k, a.beta, a.gen, a.llr_type, false)
@@ -403,6 +465,8 @@ unsigned batch_launch_grid(const BatchLaunch &bl, int64_t count, int64_t max_blo
 }
 
 BatchGrid batch_grid_for(const BatchLaunch &bl, int64_t count, int64_t max_block_stages, bool whole_words) {
+  if (bl.row_fn && row_is_faster(bl.k, bl.beta, count, (int64_t)bl.row_lds, bl.num_cu, bl.max_lds))
+    return {bl.row_fn, row_grid(count), 64, bl.row_lds};
   if (whole_words) {
     const IntKernel which =
         fastest(bl.k, count, (int64_t)bl.mx_lds[0], (int64_t)bl.mx_lds[1], bl.num_cu, bl.max_lds);
@@ -421,8 +485,11 @@ hipError_t plan_batch_launch(int k, int beta, const uint32_t *gen, int in, int m
     if (err != hipSuccess) return err;
   }
   bl->k = k;
+  bl->beta = beta;
   bl->num_cu = t_dev.num_cu;
   bl->max_lds = t_dev.max_lds;
+  bl->row_fn = nullptr;
+  bl->row_lds = 0;
   for (const bool quad : {false, true}) {
     bl->mx_fn[quad] = nullptr;
     bl->mx_lds[quad] = 0;
@@ -505,6 +572,14 @@ hipError_t plan_batch_launch(int k, int beta, const uint32_t *gen, int in, int m
   bl->lds_words_per_wave = (int)(lds_wave / 4);
   bl->items_per_wave = 1;
   bl->metric_bits = metric;
+  if (in == VIT_LLR_F32 && traced > 0 && row_takes(k, beta, gen) && row_lds_bytes(k, traced) <= t_dev.max_lds) {
+    bl->row_fn = pick_kernel_row(k, beta, true);
+    bl->row_lds = (size_t)row_lds_bytes(k, traced);
+    if (bl->row_lds > 65536) {
+      err = hipFuncSetAttribute(bl->row_fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bl->row_lds);
+      if (err != hipSuccess) return err;
+    }
+  }
   for (const bool quad : {false, true}) {
     if (in == VIT_LLR_F32 || traced <= 0 || !mx_takes(k, quad)) continue;
     const int64_t need = mx_lds_bytes(k, traced, quad);
