@@ -645,6 +645,28 @@ struct Decoder {
     lds[(grp * REGS) * 64] = acc;
   }
 
+  // The same a stage at a time, for several slots per lane and a full chip,
+  // where composing them all costs more than the chain's latency: K=9 r1/2,
+  // L = 256, 1024 blocks 36.1 us (composed 33.9), 4096 77.6 (81.6), 16384 253
+  // (275); K=8 r1/2 23.2 (20.8), 45.9 (46.1), 140 (154).
+  __device__ __forceinline__ void tb_group_stages(int grp, uint32_t &ulam) const {
+    uint32_t w[REGS], acc = 0;
+#pragma unroll
+    for (int r = 0; r < REGS; ++r) w[r] = __builtin_bitreverse32(lds[(grp * REGS + r) * 64 + lane]) >> (32 - BODY);
+#pragma unroll
+    for (int p0 = BODY - P; p0 >= 0; p0 -= P) {
+      uint32_t src = select_reg<REGS>(w, ulam >> 6);
+#pragma unroll
+      for (int q = P - 1; q >= 0; --q) {
+        // (the register that holds the slot changes only at q >= 6)
+        if (q >= 5 && q < P - 1) src = select_reg<REGS>(w, ulam >> 6);
+        ulam ^= (__builtin_amdgcn_readlane(src, (int)(ulam & 63u)) >> p0) & (1u << q);
+      }
+      acc |= ulam << p0;
+    }
+    lds[(grp * REGS) * 64] = acc;
+  }
+
   template <int Q>
   __device__ __forceinline__ void step_lane(int reg, float x, float y) {
     // unrolled by the caller, so `reg` is a constant after inlining
@@ -719,6 +741,9 @@ struct SubframeArgs {
   X(B + 7, M)
 #define VIT_X32(X, M) VIT_X8(X, 0, M) VIT_X8(X, 8, M) VIT_X8(X, 16, M) VIT_X8(X, 24, M)
 
+// Blocks of a call from which on the chip is full: four for each of 1024 SIMDs.
+constexpr int64_t kManyBlocks = 4096;
+
 // Decode one block (Sec. III): trellis stages [s, e) of a frame whose LLRs
 // start (stage 0) at `llr` and whose decoded bits start (bit 0) at byte `out`;
 // emit core bits [cs, ce).  start_known: the window starts at the frame's
@@ -732,7 +757,8 @@ struct SubframeArgs {
 template <bool SUB, int K, int BETA, bool STD, int IN>
 __device__ __forceinline__ void decode_block(Decoder<K, BETA, STD, IN> &D, const void *llr, uint8_t *out,
                                              int64_t s, int64_t e, int64_t cs, int64_t ce, bool start_known,
-                                             bool end_zero, const SubframeArgs &sa, const uint32_t *gen) {
+                                             bool end_zero, const SubframeArgs &sa, const uint32_t *gen,
+                                             int64_t nblocks) {
   using Sh = Shape<K, BETA>;
   constexpr int P = Sh::P, S = Sh::S, REGS = Sh::REGS, BODY = Sh::BODY, T = Sh::T;
   (void)T;
@@ -926,7 +952,11 @@ __device__ __forceinline__ void decode_block(Decoder<K, BETA, STD, IN> &D, const
   const uint32_t lam_start = (uint32_t)lam;
   {
     uint32_t u = (uint32_t)lam;
-    for (int grp = nbody - 1; grp >= grp_lo; --grp) D.tb_group(grp, u);
+    if (REGS > 1 && nblocks >= kManyBlocks) {
+      for (int grp = nbody - 1; grp >= grp_lo; --grp) D.tb_group_stages(grp, u);
+    } else {
+      for (int grp = nbody - 1; grp >= grp_lo; --grp) D.tb_group(grp, u);
+    }
   }
   __builtin_amdgcn_s_setprio(0);
 
@@ -995,7 +1025,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(!SUB && K >
     const int64_t s = (cs - a.v1 > 0) ? cs - a.v1 : 0;
     const int64_t e = (ce + a.v2 < a.N) ? ce + a.v2 : a.N;
     const SubframeArgs sa{a.sub_bits, a.sub_overlap, a.sub_start, a.sub_seed, blk};
-    decode_block<SUB>(D, a.llr, a.out, s, e, cs, ce, s == 0, a.terminated && (e == a.N), sa, a.gen);
+    decode_block<SUB>(D, a.llr, a.out, s, e, cs, ce, s == 0, a.terminated && (e == a.N), sa, a.gen, a.nblocks);
   }
 }
 
@@ -1028,7 +1058,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STD && K <=
     const char *base = (const char *)a.llr + it.llr_off;
     const SubframeArgs none{0, 0, 0, 0, 0};
     decode_block<false>(D, (const void *)base, a.out + it.out_off, it.s, it.e, it.cs, it.ce, (it.flags & 1) != 0,
-                        (it.flags & 2) != 0, none, a.gen);
+                        (it.flags & 2) != 0, none, a.gen, nitems);
   }
 }
 
