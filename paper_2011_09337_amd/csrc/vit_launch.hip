@@ -370,6 +370,8 @@ hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsuppor
     const hipError_t err = device_info();
     if (err != hipSuccess) return err;
   }
+  // (a shape that one block a wave cannot hold is refused, whatever the others could)
+  const bool several = a.nblocks > 1 && lds_bytes_per_block(a.k, a.beta, a.max_block_stages) <= t_dev.max_lds;
   if (a.llr_type != VIT_LLR_F32 && a.sub_bits == 0) {
     const int m = resolve_metric(a.k, a.beta, a.llr_type, a.metric_bits, a.max_block_stages, why);
     if (m < 0) {
@@ -377,7 +379,7 @@ hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsuppor
       return hipSuccess;
     }
     if (m == kMetric16) return launch_blocked16(a, stream, unsupported, why);
-    if (a.nblocks > 1) {
+    if (several) {
       const int64_t traced = a.L + a.v2;
       const int64_t mx = mx_takes(a.k, false) ? mx_lds_bytes(a.k, traced, false) : 0;
       const int64_t quad = mx_takes(a.k, true) ? mx_lds_bytes(a.k, traced, true) : 0;
@@ -396,7 +398,7 @@ hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsuppor
       *why = "int8 block too long for exact integers in fp32";
       return hipSuccess;
     }
-  } else if (a.sub_bits == 0 && a.nblocks > 1 && row_takes(a.k, a.beta, a.gen)) {
+  } else if (a.sub_bits == 0 && several && row_takes(a.k, a.beta, a.gen)) {
     const int64_t lds = row_lds_bytes(a.k, a.L + a.v2);
     if (row_is_faster(a.k, a.beta, a.nblocks, lds, t_dev.num_cu, t_dev.max_lds)) return launch_blocked_row(a, lds, stream);
   }

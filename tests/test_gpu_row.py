@@ -76,3 +76,12 @@ def test_batches(dev, name, kind):  # noqa: F811
     torch.cuda.synchronize()
     b.close()
     np.testing.assert_array_equal(outs[0].cpu().numpy(), outs[1].cpu().numpy())
+
+
+def test_refused_block_length(dev):  # noqa: F811
+    # a block that one wave cannot hold is refused, though four of K=3's would fit beside each other
+    torch, vit = dev
+    L, blocks = 24000, 5300
+    llr = torch.empty(2 * (L * blocks + 2), dtype=torch.float32, device="cuda")
+    with pytest.raises(Exception, match="survivor storage"):
+        vit.decode(vit.make_code(3, (0o7, 0o5)), llr, L * blocks, L, 15)
