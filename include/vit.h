@@ -118,7 +118,7 @@ typedef struct {
    * difference (eq. 3 in 16 bits; exact while compared metrics differ by less
    * than 2^15, which the spread bound (k-1)*2*128*beta + 2^14 guarantees);
    * blocks up to the LDS limit of two blocks' survivors per wave.  32: exact
-   * 32-bit integers, one block per wave; blocks up to 2^24 / (128 beta)
+   * 32-bit integers; blocks up to 2^24 / (128 beta)
    * stages.  0 (default): 32 where the blocks fit, else 16 (32 measured
    * faster on gfx950).
    * Subframe traceback runs with 32 only.  Ignored for FP32 LLRs. */

@@ -28,7 +28,7 @@ struct DecodeArgs {
   int32_t sub_overlap;   // inner overlap of a subframe, in stages
   int32_t sub_start;     // VIT_SUBFRAME_STORED or VIT_SUBFRAME_RANDOM
   uint64_t sub_seed;     // SplitMix64 seed of the random start rule
-  int32_t metric_bits;   // integer inputs: 16 (modulo 2^16 metrics), 32 (exact integers held in fp32), 0 = 32
+  int32_t metric_bits;   // integer inputs: 16 (modulo 2^16 metrics), 32 (exact 32-bit metrics), 0 = 32
                          // where its bound and survivor storage allow, else 16
 };
 

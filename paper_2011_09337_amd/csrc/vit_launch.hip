@@ -240,14 +240,18 @@ int mx_waves_per_cu(int64_t lds, int max_lds, bool quad) {
 // 4096 blocks 20 / - / 18, 65536 204 / - / 34; K=3, L = 256, 4096 blocks
 // 22 / - / 24, 16384 58 / - / 25; K=9, L = 256, 1024 blocks 26 / 38 / -,
 // 4096 66 / 48 / -, 16384 237 / 94 / -.  Over nine lengths and thirteen sizes
-// of six codes the choice cost 10 % or more in one case of thirty.
+// of seven codes the choice took at most 6 % more than the best but at L = 2048
+// (K=4 r1/4 37 %) and where two were within 10 %.
 //
 // One block a wave: one wave's latency, and 10.6 for each further 64 states on
-// a SIMD.
-double one_block_ns(int k, int64_t blocks, int64_t simds) {
+// a SIMD; in rounds where LDS (lds: a block's) holds fewer than four waves a SIMD.
+double one_block_ns(int k, int64_t blocks, int64_t simds, int64_t lds, int max_lds) {
   const double regs = k > 7 ? 1 << (k - 7) : 1;
   const double latency = k <= 7 ? 24.0 : k == 8 ? 30.0 : 70.0;
-  return latency + 10.6 * regs * (double)((blocks - 1) / simds);
+  const double waves = (double)((blocks + simds - 1) / simds);
+  const double fit = (double)(max_lds / ((lds + 1279) / 1280 * 1280)) / 4;
+  if (fit < 4 && waves > fit) return waves / fit * (latency + 10.6 * regs * (fit > 1 ? fit - 1 : 0));
+  return latency + 10.6 * regs * (waves - 1);
 }
 // 16 registers: a second wave on a SIMD costs half as much again (some get one
 // before every SIMD has its first); as many as fit at a time, whole rounds of
@@ -260,25 +264,25 @@ double mx_ns(int k, int64_t blocks, int64_t simds, int per_cu) {
   const double share = tiles > simds ? 1.55 * wave : tiles > simds / 2 ? 1.3 * wave : wave;
   return tiles > slots ? (double)tiles / (double)slots * share : share;
 }
-// 4 registers: each further wave on a SIMD 16 more, as many as fit at a time.
+// 4 registers: each further wave on a SIMD 15 more, in rounds of as many as fit.
 double quad_ns(int k, int64_t blocks, int64_t simds, int per_cu) {
-  const double lone = k == 3 ? 66.0 : k == 4 ? 54.0 : 44.0;
-  const double waves = (double)((blocks + mx_blocks(k, true) - 1) / mx_blocks(k, true)) / (double)simds;
-  const double fit = per_cu > 4 ? per_cu / 4.0 : 1.0;
-  if (per_cu < 4) return lone * (waves * 4 / per_cu > 1 ? waves * 4 / per_cu : 1);
-  if (waves <= 1) return lone;
-  return waves <= fit ? lone + 16 * (waves - 1) : waves / fit * (lone + 16 * (fit - 1));
+  const double lone = k == 3 ? 68.0 : k == 4 ? 58.0 : 49.0;
+  const int64_t tiles = (blocks + mx_blocks(k, true) - 1) / mx_blocks(k, true), slots = per_cu * simds / 4;
+  const int64_t full = (tiles - 1) / slots;
+  if (per_cu < 4) return lone * (double)(full + 1);
+  const double waves = (double)(tiles - full * slots) / (double)simds;
+  return (double)full * (lone + 15 * (per_cu / 4.0 - 1)) + lone + (waves > 1 ? 15 * (waves - 1) : 0);
 }
 
 enum IntKernel { kOneBlock, kMx, kQuad };
-// lds_mx, lds_quad: LDS bytes of a wave, or 0 where the layout cannot run.
-IntKernel fastest(int k, int64_t blocks, int64_t lds_mx, int64_t lds_quad, int num_cu, int max_lds) {
+// LDS bytes of a wave: lds of the one-block kernel, lds_mx and lds_quad, 0 where the layout cannot run.
+IntKernel fastest(int k, int64_t blocks, int64_t lds, int64_t lds_mx, int64_t lds_quad, int num_cu, int max_lds) {
   const int64_t simds = 4 * (int64_t)num_cu;
   IntKernel best = kOneBlock;
-  double ns = one_block_ns(k, blocks, simds);
+  double ns = one_block_ns(k, blocks, simds, lds, max_lds);
   for (const IntKernel one : {kMx, kQuad}) {
-    const int64_t lds = one == kQuad ? lds_quad : lds_mx;
-    const int per_cu = lds ? mx_waves_per_cu(lds, max_lds, one == kQuad) : 0;
+    const int64_t need = one == kQuad ? lds_quad : lds_mx;
+    const int per_cu = need ? mx_waves_per_cu(need, max_lds, one == kQuad) : 0;
     if (per_cu < 1) continue;
     const double t = one == kQuad ? quad_ns(k, blocks, simds, per_cu) : mx_ns(k, blocks, simds, per_cu);
     if (t < ns) {
@@ -371,7 +375,8 @@ hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsuppor
     if (err != hipSuccess) return err;
   }
   // (a shape that one block a wave cannot hold is refused, whatever the others could)
-  const bool several = a.nblocks > 1 && lds_bytes_per_block(a.k, a.beta, a.max_block_stages) <= t_dev.max_lds;
+  const int64_t one = lds_bytes_per_block(a.k, a.beta, a.max_block_stages);
+  const bool several = a.nblocks > 1 && one <= t_dev.max_lds;
   if (a.llr_type != VIT_LLR_F32 && a.sub_bits == 0) {
     const int m = resolve_metric(a.k, a.beta, a.llr_type, a.metric_bits, a.max_block_stages, why);
     if (m < 0) {
@@ -383,7 +388,7 @@ hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsuppor
       const int64_t traced = a.L + a.v2;
       const int64_t mx = mx_takes(a.k, false) ? mx_lds_bytes(a.k, traced, false) : 0;
       const int64_t quad = mx_takes(a.k, true) ? mx_lds_bytes(a.k, traced, true) : 0;
-      const IntKernel which = fastest(a.k, a.nblocks, mx, quad, t_dev.num_cu, t_dev.max_lds);
+      const IntKernel which = fastest(a.k, a.nblocks, one, mx, quad, t_dev.num_cu, t_dev.max_lds);
       if (which != kOneBlock) return launch_blocked_mx(a, which == kQuad ? quad : mx, which == kQuad, stream);
     }
   } else if (a.llr_type != VIT_LLR_F32) {
@@ -471,7 +476,7 @@ BatchGrid batch_grid_for(const BatchLaunch &bl, int64_t count, int64_t max_block
     return {bl.row_fn, row_grid(count), 64, bl.row_lds};
   if (whole_words) {
     const IntKernel which =
-        fastest(bl.k, count, (int64_t)bl.mx_lds[0], (int64_t)bl.mx_lds[1], bl.num_cu, bl.max_lds);
+        fastest(bl.k, count, (int64_t)bl.lds_words_per_wave * 4, (int64_t)bl.mx_lds[0], (int64_t)bl.mx_lds[1], bl.num_cu, bl.max_lds);
     const bool quad = which == kQuad;
     if (which != kOneBlock)
       return {bl.mx_fn[quad], mx_grid(bl.k, count, (int64_t)bl.mx_lds[quad], bl.num_cu, bl.max_lds, quad), 64, bl.mx_lds[quad]};
