@@ -259,7 +259,7 @@ double one_block_ns(int k, int64_t blocks, int64_t simds, int64_t lds, int max_l
 double mx_ns(int k, int64_t blocks, int64_t simds, int per_cu) {
   const int64_t slots = per_cu * simds / 4;
   const int64_t tiles = (blocks + mx_blocks(k, false) - 1) / mx_blocks(k, false);
-  const double wave = k == 6 ? 106.0 : k == 7 ? 95.0 : 115.0;
+  const double wave = k == 6 ? 106.0 : k == 7 ? 95.0 : k == 8 ? 100.0 : 115.0;
   if (per_cu <= 4) return (double)((tiles + slots - 1) / slots) * wave;
   const double share = tiles > simds ? 1.55 * wave : tiles > simds / 2 ? 1.3 * wave : wave;
   return tiles > slots ? (double)tiles / (double)slots * share : share;
