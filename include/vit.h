@@ -221,6 +221,8 @@ typedef struct {
 typedef struct vit_plan vit_plan;
 
 int vit_plan_create(vit_plan **plan);
+/* Waits until the plan's decodes have ended, whatever stream they run on: the
+ * workspaces they were given can be freed or reused after it returns. */
 void vit_plan_destroy(vit_plan *plan);
 
 /* Path metrics of the plan's integer decodes, as vit_opts.metric_bits: 0
@@ -239,8 +241,8 @@ int vit_batch_workspace_size(const vit_code *codes, int32_t ncodes, const vit_fr
  * code, or NULL for the plan's autotuned shapes (default L = 256, v = 5k for k <= 7 and 8(k-1) above,
  * 1 wave per workgroup when not tuned); workspace: device memory of at least
  * vit_batch_workspace_size bytes, 256-byte aligned, not used by concurrent
- * calls.  Asynchronous on `stream`; the host staging of the previous use of
- * a staging slot is waited for before it is rewritten.
+ * calls.  Asynchronous on `stream`, up to two calls ahead of the device: a call
+ * waits for the end of the one before the last.
  * Errors: VIT_EINVAL for bad codes, frames outside the buffers, bad tunings
  * or a small workspace; VIT_EUNSUPPORTED for shapes without a kernel (LDS);
  * VIT_EDEVICE for HIP failures. */

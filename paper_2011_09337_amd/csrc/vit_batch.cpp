@@ -27,7 +27,7 @@
 struct vit_plan {
   void *staging[2] = {nullptr, nullptr};
   size_t staging_cap[2] = {0, 0};
-  hipEvent_t done[2] = {nullptr, nullptr};
+  hipEvent_t done[2] = {nullptr, nullptr};  // after the last kernel of the slot's call
   bool pending[2] = {false, false};
   int slot = 0;
 
@@ -388,6 +388,8 @@ int vit_plan_create(vit_plan **plan) {
   return VIT_OK;
 }
 
+// Returns when the plan's calls have ended: their kernels read the staging and
+// the caller's workspace, which may be given back after this.
 void vit_plan_destroy(vit_plan *plan) {
   if (!plan) return;
   for (int i = 0; i < 2; ++i) {
@@ -491,7 +493,8 @@ static int decode_batch_impl(vit_plan *plan, const vit_code *codes, int32_t ncod
     plan->have_launch = true;
   }
 
-  // the staging slot's previous records must have been read before it is rewritten
+  // The slot's previous call must have ended: its staging is rewritten, and its
+  // event, which vit_plan_destroy waits for, is recorded again.
   const int slot = plan->slot;
   if (plan->pending[slot]) {
     he = hipEventSynchronize(plan->done[slot]);
@@ -500,6 +503,12 @@ static int decode_batch_impl(vit_plan *plan, const vit_code *codes, int32_t ncod
   }
   st = ensure_staging(plan, slot, (size_t)nrecords * sizeof(vit::FrameRecord));
   if (st) return st;
+  if (!plan->done[slot]) {
+    // a timing event: on this runtime recording one costs about a quarter
+    // of recording an event with timing disabled
+    he = hipEventCreate(&plan->done[slot]);
+    if (he != hipSuccess) return vit::api_fail_hip(he, "hipEventCreate");
+  }
   vit::ExpandArgs ex;
   memset(&ex, 0, sizeof(ex));
   ex.records = (const vit::FrameRecord *)plan->staging[slot];
@@ -510,18 +519,6 @@ static int decode_batch_impl(vit_plan *plan, const vit_code *codes, int32_t ncod
                 &ex);
   he = vit::launch_expand(ex, (hipStream_t)stream);
   if (he != hipSuccess) return vit::api_fail_hip(he, "work list kernel launch");
-  if (!plan->done[slot]) {
-    // a timing event: on this runtime recording one costs about a quarter
-    // of recording an event with timing disabled
-    he = hipEventCreate(&plan->done[slot]);
-    if (he != hipSuccess) return vit::api_fail_hip(he, "hipEventCreate");
-  }
-  // (the records are read by the first kernel alone: once it is done the slot
-  // can be rewritten)
-  he = hipEventRecord(plan->done[slot], (hipStream_t)stream);
-  if (he != hipSuccess) return vit::api_fail_hip(he, "hipEventRecord");
-  plan->pending[slot] = true;
-  plan->slot = slot ^ 1;
 
   // one kernel per code, one after another, the code with the most work per
   // bit (states x rate) first: measured faster than running them side by side
@@ -529,7 +526,7 @@ static int decode_batch_impl(vit_plan *plan, const vit_code *codes, int32_t ncod
   vit::frames_of_whole_words(ncodes, frames, nframes, whole);
   int order[kMaxCodes];
   vit::batch_code_order(codes, ncodes, order);
-  for (int oi = 0; oi < ncodes; ++oi) {
+  for (int oi = 0; oi < ncodes && he == hipSuccess; ++oi) {
     const int c = order[oi];
     if (counts[c] == 0) continue;
     vit::BatchArgs args;
@@ -544,10 +541,19 @@ static int decode_batch_impl(vit_plan *plan, const vit_code *codes, int32_t ncod
     const vit::BatchGrid g =
         vit::batch_grid_for(plan->bl[c], counts[c], (int64_t)shape[c].L + shape[c].v, whole[c]);
     he = hipLaunchKernel(g.fn, dim3(g.grid), dim3(g.block), kargs, g.lds, (hipStream_t)stream);
-    if (he != hipSuccess) return vit::api_fail_hip(he, "batch kernel launch");
   }
-  he = hipGetLastError();
+  if (he == hipSuccess) he = hipGetLastError();
+  // after the last kernel launched (also where one failed): once it has passed,
+  // nothing of this call reads the staging or the caller's workspace
+  const hipError_t recorded = hipEventRecord(plan->done[slot], (hipStream_t)stream);
+  if (recorded == hipSuccess) {
+    plan->pending[slot] = true;
+    plan->slot = slot ^ 1;
+  } else {
+    (void)hipStreamSynchronize((hipStream_t)stream);
+  }
   if (he != hipSuccess) return vit::api_fail_hip(he, "batch kernel launch");
+  if (recorded != hipSuccess) return vit::api_fail_hip(recorded, "hipEventRecord");
   return VIT_OK;
 }
 
