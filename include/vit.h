@@ -244,18 +244,20 @@ int vit_batch_workspace_size(const vit_code *codes, int32_t ncodes, const vit_fr
  * calls.  Asynchronous on `stream`, up to two calls ahead of the device: a call
  * waits for the end of the one before the last.
  * Errors: VIT_EINVAL for bad codes, frames outside the buffers, bad tunings
- * or a small workspace; VIT_EUNSUPPORTED for shapes without a kernel (LDS);
- * VIT_EDEVICE for HIP failures. */
+ * or a small workspace; VIT_EUNSUPPORTED for shapes without a kernel (LDS) and
+ * for a stream that is being captured (the work list is written anew by every
+ * call: a replay would decode what a later call left in the plan's staging;
+ * vit_decode_ex can be captured); VIT_EDEVICE for HIP failures. */
 int vit_decode_batch(vit_plan *plan, const vit_code *codes, int32_t ncodes, const vit_frame *frames,
                      int32_t nframes, const void *llr, int64_t llr_count, int32_t llr_type, uint8_t *out,
                      int64_t out_bytes, const vit_tuning *tune, void *workspace, size_t workspace_bytes,
                      void *stream);
 
 /* For callers that cannot allocate: code that must not call hipMalloc or
- * create graphs (work under HIP graph capture, tight serving loops,
- * harnesses that forbid allocation).  The same decode as vit_decode_batch,
- * bit for bit, without a plan or workspace: the work list (header and work
- * items) lives in a fixed device array inside the library of 256 +
+ * create graphs (tight serving loops, harnesses that forbid allocation; it
+ * waits for its stream, so that the stream cannot be under capture).  The same
+ * decode as vit_decode_batch, bit for bit, without a plan or workspace: the
+ * work list (header and work items) lives in a fixed device array inside the library of 256 +
  * VIT_STATIC_BATCH_MAX_ITEMS * 40 bytes (10.5 MB), one copy per GPU the
  * library runs on, held until the process ends; the host builds it in fixed
  * host arrays of the same capacity.  The call makes no hipMalloc, hipFree,

@@ -460,11 +460,20 @@ static int decode_batch_impl(vit_plan *plan, const vit_code *codes, int32_t ncod
     return api_fail(VIT_EINVAL, "workspace of %zu bytes, %zu needed", workspace_bytes, need);
   if (total >= ((int64_t)1 << 31)) return api_fail(VIT_EUNSUPPORTED, "too many blocks");
 
+  // A captured call would be replayed with the plan's staging as later calls
+  // left it: refused before anything of the plan changes.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  hipError_t he = hipStreamIsCapturing((hipStream_t)stream, &capture);
+  if (he != hipSuccess) return vit::api_fail_hip(he, "hipStreamIsCapturing");
+  if (capture != hipStreamCaptureStatusNone)
+    return api_fail(VIT_EUNSUPPORTED, "the stream is being captured: a batch's work list is written anew by every call "
+                                      "(vit_decode_ex can be captured)");
+
   // launch shapes (LDS sized for the longest block a shape can produce),
   // kept while codes and shapes stay the same; nothing is launched or kept
   // unless every code has one
   int dev = 0;
-  hipError_t he = hipGetDevice(&dev);
+  he = hipGetDevice(&dev);
   if (he != hipSuccess) return vit::api_fail_hip(he, "hipGetDevice");
   vit_plan::Key key;
   key.llr_type = llr_type;
