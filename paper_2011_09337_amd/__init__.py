@@ -122,12 +122,16 @@ class Batch:
     codes: list of vit_code; frames: a FRAME_DTYPE array (passed to the C ABI
     without copying) or a list of (code_id, terminated, n, llr_off, out_off).
     The workspace is a torch uint8 tensor sized by vit_batch_workspace_size
-    for the largest frame list seen."""
+    for the largest frame list seen.  One that a larger one (of at least twice
+    its size) replaces is kept until `close`, which waits for the plan's
+    decodes: they may still read it, on streams that the allocator does not
+    know of."""
 
     def __init__(self, device="cuda", metric_bits=0, tune_tolerance=None):
         self.plan = vit_plan_create()
         self.device = device
         self.ws = None
+        self._replaced = []
         if metric_bits:
             _lib.vit_plan_set_metric_bits(self.plan, metric_bits)
         if tune_tolerance is not None:
@@ -137,6 +141,7 @@ class Batch:
         if self.plan is not None:
             vit_plan_destroy(self.plan)
             self.plan = None
+            self._replaced.clear()
 
     def __del__(self):
         try:
@@ -148,6 +153,8 @@ class Batch:
         import torch
         need = vit_batch_workspace_size(codes_arr, frames_arr, tune_arr)
         if self.ws is None or self.ws.numel() < need + 256:
+            if self.ws is not None:
+                self._replaced.append(self.ws)
             self.ws = torch.empty(max(need, 4096) * 2 + 256, dtype=torch.uint8, device=self.device)
         base = self.ws.data_ptr()
         aligned = (base + 255) // 256 * 256

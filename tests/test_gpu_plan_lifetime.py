@@ -1,6 +1,7 @@
 """What outlives a call of `Batch.decode`: a plan that is closed or dropped has
 waited for its decodes, on every stream they were queued on, so that nothing
-reads its workspace any more."""
+reads its workspace any more; a workspace that a larger one replaces is not
+handed out again while a decode on another stream still reads it."""
 import numpy as np
 import pytest
 
@@ -57,3 +58,20 @@ def test_a_closed_plan_has_no_work_left_on_an_earlier_stream(dev):  # noqa: F811
     assert first.query() and second.query()
     n = 4096 // 8
     np.testing.assert_array_equal(out[0].cpu().numpy()[:n], out[1].cpu().numpy()[:n])
+
+
+def test_a_replaced_workspace_is_held(dev):  # noqa: F811
+    torch, vit = dev
+    codes, frames, llr, tune, nbytes = _batch(dev)
+    side = torch.cuda.Stream()
+    out = torch.zeros(nbytes, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    b = vit.Batch()
+    b.decode(codes, frames[:8], llr, out, tune=[tune], stream=side)
+    old, size = b.ws.data_ptr(), b.ws.numel()
+    b.decode(codes, frames, llr, out, tune=[tune], stream=side)
+    assert b.ws.numel() >= 2 * size
+    others = [torch.empty(size, dtype=torch.uint8, device="cuda") for _ in range(4)]
+    held = all(old != x.data_ptr() for x in others)
+    b.close()
+    assert held and side.query()
