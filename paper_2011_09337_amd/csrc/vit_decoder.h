@@ -856,11 +856,17 @@ __device__ __forceinline__ void decode_block(Decoder<K, BETA, STD, IN> &D, const
     // body offset pos (q = pos mod P) the decoded bit of stage t is bit q of
     // u (the state's newest input, rotated into place) and following the
     // survivor flips bit q by the stored word bit (decision XOR own bit q).
-    // The stages down to a period's end are taken one by one; then the words
-    // are composed (see compose) and a chain takes a period at a time, whose
-    // decoded bits are those of its slot (a stage at a time throughout:
-    // K=7 r1/2, 2^22 bits, L = 512, f0 = 56, w = 45 83.1 us, so 76.2).  Decoded bits go to
-    // one LDS byte each, after the survivors.
+    // A chain goes a stage at a time; or it takes the stages down to a period's
+    // end one by one, the words of the whole block are composed (see compose),
+    // and it takes a period at a time, whose decoded bits are those of its slot.
+    // Composing a word costs what the longest chain saves in about two stages
+    // (k >= 6; one below), so that the first is the faster where the block's words
+    // are many beside the chain (FP32 r1/2, by stage / by period, us: K=9, 2^20
+    // bits, L = 2048, f0 = 64, w = 100 213 / 228; K=8, L = 2048, f0 = 64, w = 20
+    // 127 / 141; K=7, 2^22 bits, L = 512, f0 = 56, w = 45 80 / 76; K=9, 2^20 bits,
+    // L = 2048, f0 = 64, w = 400 245 / 235).  Over 4704 lengths and sizes of seven
+    // codes at most 5 % off the better of the two.  Decoded bits go to one LDS
+    // byte each, after the survivors.
     uint8_t *dbytes = (uint8_t *)(D.lds + nbody * REGS * 64);
     const int c = D.lane;
     int t = 0, a_lo = 1, b_end = 0, pos = P - 1, bdy = 0;
@@ -885,43 +891,57 @@ __device__ __forceinline__ void decode_block(Decoder<K, BETA, STD, IN> &D, const
       t = x - 1;
     }
     auto word = [&]() -> uint32_t { return D.lds[(bdy * REGS + (int)(u >> 6)) * 64 + (int)(u & 63u)]; };
-    for (int q = pos % P; __builtin_amdgcn_ballot_w64(t >= a_lo && q != P - 1);) {
-      if (t >= a_lo && q != P - 1) {
-        if (t < b_end) dbytes[t - (int)cs] = (uint8_t)((u >> q) & 1u);
-        u ^= ((word() >> (BODY - 1 - pos)) & 1u) << q;
-        q = q == 0 ? P - 1 : q - 1;
-        --t;
-        if (--pos < 0) {
-          pos = BODY - 1;
-          --bdy;
-        }
-      }
-    }
     auto lds_phase = [] {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
-    lds_phase();
-    for (int grp = ((int)(cs - s) + r) / BODY; grp < nbody; ++grp) {
-      uint32_t w[REGS];
-      D.composed(grp, w);
+    int q = pos % P;
+    auto stage = [&] {
+      if (t < b_end) dbytes[t - (int)cs] = (uint8_t)((u >> q) & 1u);
+      u ^= ((word() >> (BODY - 1 - pos)) & 1u) << q;
+      q = q == 0 ? P - 1 : q - 1;
+      --t;
+      if (--pos < 0) {
+        pos = BODY - 1;
+        --bdy;
+      }
+    };
+    const int grp_lo = ((int)(cs - s) + r) / BODY;
+    const int core = (int)(ce - cs), past = (int)(e - ce);
+    int longest = (f0 < core ? f0 : core) + (sa.w > past ? sa.w : past);
+    if (longest > core + past) longest = core + past;
+    constexpr int kDear = K >= 8 ? 7 : K >= 6 ? 8 : 4;  // quarters of a stage a word
+    if (4 * longest <= kDear * (nbody - grp_lo) * REGS) {
+      const int len = t - a_lo + 1;
+      for (int i = 0; i < longest; ++i) {
+        if (i < len) stage();
+      }
+    } else {
+      while (__builtin_amdgcn_ballot_w64(t >= a_lo && q != P - 1)) {
+        if (t >= a_lo && q != P - 1) stage();
+      }
+      lds_phase();
+      for (int grp = grp_lo; grp < nbody; ++grp) {
+        uint32_t w[REGS];
+        D.composed(grp, w);
 #pragma unroll
-      for (int rr = 0; rr < REGS; ++rr) D.lds[(grp * REGS + rr) * 64 + D.lane] = w[rr];
-    }
-    lds_phase();
-    while (__builtin_amdgcn_ballot_w64(t >= a_lo)) {
-      if (t >= a_lo) {
-        const uint32_t flips = (word() >> (pos - (P - 1))) & (uint32_t)(S - 1);
+        for (int rr = 0; rr < REGS; ++rr) D.lds[(grp * REGS + rr) * 64 + D.lane] = w[rr];
+      }
+      lds_phase();
+      while (__builtin_amdgcn_ballot_w64(t >= a_lo)) {
+        if (t >= a_lo) {
+          const uint32_t flips = (word() >> (pos - (P - 1))) & (uint32_t)(S - 1);
 #pragma unroll
-        for (int q = P - 1; q >= 0; --q, --t) {
-          if (t < b_end && t >= a_lo) dbytes[t - (int)cs] = (uint8_t)((u >> q) & 1u);
-        }
-        u ^= flips;
-        pos -= P;
-        if (pos < 0) {
-          pos = BODY - 1;
-          --bdy;
+          for (int qq = P - 1; qq >= 0; --qq, --t) {
+            if (t < b_end && t >= a_lo) dbytes[t - (int)cs] = (uint8_t)((u >> qq) & 1u);
+          }
+          u ^= flips;
+          pos -= P;
+          if (pos < 0) {
+            pos = BODY - 1;
+            --bdy;
+          }
         }
       }
     }
