@@ -467,6 +467,22 @@ int vit_abi_version(void);
  * VIT_ENOMEM (inside the serving engine it fails the server with VIT_ENOMEM). */
 int vit_debug_fail_allocations(int32_t count);
 
+/* Test hook for the choice of kernels (not part of the decode; host only): which
+ * one decodes `blocks` blocks of L core bits and overlap v (v1 on the left, -1 =
+ * floor(v/2)), one trace per block, 32-bit integer metrics, as a stream or as one
+ * code's part of a batch (whose frames hold at least four LLRs), on a device of
+ * num_cu compute units with lds_bytes of LDS per workgroup.  The results are the
+ * same whichever runs.  VIT_EINVAL for bad arguments; VIT_EUNSUPPORTED where no
+ * such kernel takes the blocks. */
+enum {
+  VIT_KERNEL_ONE_BLOCK = 0, /* one block a wave                                    */
+  VIT_KERNEL_MX16 = 1,      /* integers on the matrix cores, 16 metric registers   */
+  VIT_KERNEL_MX4 = 2,       /* the same, 4 metric registers                        */
+  VIT_KERNEL_ROW = 3        /* FP32, four blocks a wave                            */
+};
+int vit_debug_kernel(const vit_code *code, int32_t llr_type, int64_t blocks, int32_t L, int32_t v, int32_t v1,
+                     int32_t num_cu, int32_t lds_bytes, int32_t *kernel);
+
 #ifdef __cplusplus
 }
 #endif

@@ -161,6 +161,8 @@ lib.vit_abi_version.argtypes = []
 lib.vit_abi_version.restype = C.c_int
 lib.vit_debug_fail_allocations.argtypes = [C.c_int32]
 lib.vit_debug_fail_allocations.restype = C.c_int
+lib.vit_debug_kernel.argtypes = [C.POINTER(vit_code), C.c_int32, C.c_int64] + [C.c_int32] * 5 + [C.POINTER(C.c_int32)]
+lib.vit_debug_kernel.restype = C.c_int
 lib.vit_plan_get_tuning.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.POINTER(C.c_int32)]
 lib.vit_plan_get_tuning.restype = C.c_int
 lib.vit_plan_set_tuning.argtypes = [C.c_void_p, C.c_void_p, C.c_int32]

@@ -147,6 +147,23 @@ int vit_debug_fail_allocations(int32_t count) {
   return VIT_OK;
 }
 
+int vit_debug_kernel(const vit_code *code, int32_t llr_type, int64_t blocks, int32_t L, int32_t v, int32_t v1,
+                     int32_t num_cu, int32_t lds_bytes, int32_t *kernel) {
+  vit::api_clear_error();
+  const int st = check_code(code);
+  if (st) return st;
+  if (!kernel) return api_fail(VIT_EINVAL, "kernel is NULL");
+  if (llr_type != VIT_LLR_F32 && llr_type != VIT_LLR_I8 && llr_type != VIT_LLR_HARD)
+    return api_fail(VIT_EINVAL, "unknown llr_type %d", llr_type);
+  if (blocks < 1 || L < 1 || v < 0 || v1 < -1 || v1 > v || num_cu < 1 || lds_bytes < 1)
+    return api_fail(VIT_EINVAL, "blocks, L, num_cu and lds_bytes must be positive, v1 in [-1, v]");
+  const int64_t traced = (int64_t)L + v - (v1 < 0 ? v / 2 : v1);
+  const int which = vit::kernel_for(code->k, code->beta, code->gen, llr_type, blocks, (int64_t)L + v, traced, num_cu, lds_bytes);
+  if (which < 0) return api_fail(VIT_EUNSUPPORTED, "no 32-bit kernel takes blocks of %lld stages", (long long)L + v);
+  *kernel = which;
+  return VIT_OK;
+}
+
 vit_opts vit_opts_default(void) {
   vit_opts o;
   memset(&o, 0, sizeof(o));

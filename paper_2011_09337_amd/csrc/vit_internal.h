@@ -100,6 +100,14 @@ bool fp32_integer_exact(int beta, int64_t max_block_stages);
 hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsupported,
                           const char **why);
 
+// The kernel (VIT_KERNEL_*) for `blocks` blocks of at most max_block_stages
+// stages, `traced` of them from a block's first core bit on, one trace a block
+// and 32-bit integer metrics, on a device of num_cu compute units with max_lds
+// bytes of LDS a workgroup; -1 where none takes them.  What launch_blocked and
+// batch_grid_for choose.
+int kernel_for(int k, int beta, const uint32_t *gen, int in, int64_t blocks, int64_t max_block_stages, int64_t traced,
+               int num_cu, int max_lds);
+
 // Kernel instance and launch shape of a batched decode for one code.
 struct BatchLaunch {
   const void *fn;            // __global__ function

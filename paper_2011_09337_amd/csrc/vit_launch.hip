@@ -7,6 +7,8 @@
 #include "vit_decoder_row.h"
 #include "vit_shapes.h"
 
+#include <utility>
+
 namespace vit {
 namespace {
 
@@ -274,25 +276,6 @@ double quad_ns(int k, int64_t blocks, int64_t simds, int per_cu) {
   return (double)full * (lone + 15 * (per_cu / 4.0 - 1)) + lone + (waves > 1 ? 15 * (waves - 1) : 0);
 }
 
-enum IntKernel { kOneBlock, kMx, kQuad };
-// LDS bytes of a wave: lds of the one-block kernel, lds_mx and lds_quad, 0 where the layout cannot run.
-IntKernel fastest(int k, int64_t blocks, int64_t lds, int64_t lds_mx, int64_t lds_quad, int num_cu, int max_lds) {
-  const int64_t simds = 4 * (int64_t)num_cu;
-  IntKernel best = kOneBlock;
-  double ns = one_block_ns(k, blocks, simds, lds, max_lds);
-  for (const IntKernel one : {kMx, kQuad}) {
-    const int64_t need = one == kQuad ? lds_quad : lds_mx;
-    const int per_cu = need ? mx_waves_per_cu(need, max_lds, one == kQuad) : 0;
-    if (per_cu < 1) continue;
-    const double t = one == kQuad ? quad_ns(k, blocks, simds, per_cu) : mx_ns(k, blocks, simds, per_cu);
-    if (t < ns) {
-      ns = t;
-      best = one;
-    }
-  }
-  return best;
-}
-
 // Workgroups (of one wave): one per tile, refilled by the dispatcher, where
 // several waves share a SIMD; where LDS allows at most one per SIMD, that many
 // persistent waves (K=7, L = 512, 2^24 bits, 16 registers: 117 us against 149,
@@ -366,7 +349,57 @@ hipError_t launch_blocked_row(const DecodeArgs &a, int64_t lds, hipStream_t stre
   return hipGetLastError();
 }
 
+// ---- the choice between them
+
+// LDS bytes of a wave of each kernel for blocks of at most max_block_stages
+// stages, `traced` of them from the first core bit on; 0 where that kernel
+// cannot take them.
+struct Layouts {
+  int64_t one, mx, quad, row;
+};
+Layouts layouts(int k, int beta, const uint32_t *gen, int in, int64_t max_block_stages, int64_t traced, int max_lds) {
+  auto fits = [&](int64_t lds) { return lds <= max_lds ? lds : 0; };
+  Layouts l = {fits(lds_bytes_per_block(k, beta, max_block_stages)), 0, 0, 0};
+  // (a shape that one block a wave cannot hold is refused, whatever the others could)
+  if (!l.one || traced <= 0) return l;
+  if (in == VIT_LLR_F32) {
+    if (row_takes(k, beta, gen)) l.row = fits(row_lds_bytes(k, traced));
+  } else {
+    if (mx_takes(k, false)) l.mx = fits(mx_lds_bytes(k, traced, false));
+    if (mx_takes(k, true)) l.quad = fits(mx_lds_bytes(k, traced, true));
+  }
+  return l;
+}
+
+// The kernel that takes the least time for `blocks` blocks.
+int choose_kernel(int k, int beta, const Layouts &l, int64_t blocks, int num_cu, int max_lds) {
+  if (blocks < 2) return VIT_KERNEL_ONE_BLOCK;
+  if (l.row && row_is_faster(k, beta, blocks, l.row, num_cu, max_lds)) return VIT_KERNEL_ROW;
+  const int64_t simds = 4 * (int64_t)num_cu;
+  int best = VIT_KERNEL_ONE_BLOCK;
+  double ns = l.mx || l.quad ? one_block_ns(k, blocks, simds, l.one, max_lds) : 0;
+  for (const bool quad : {false, true}) {
+    const int64_t lds = quad ? l.quad : l.mx;
+    if (!lds) continue;
+    const int per_cu = mx_waves_per_cu(lds, max_lds, quad);
+    if (per_cu < 1) continue;
+    const double t = quad ? quad_ns(k, blocks, simds, per_cu) : mx_ns(k, blocks, simds, per_cu);
+    if (t < ns) {
+      ns = t;
+      best = quad ? VIT_KERNEL_MX4 : VIT_KERNEL_MX16;
+    }
+  }
+  return best;
+}
+
 }  // namespace
+
+int kernel_for(int k, int beta, const uint32_t *gen, int in, int64_t blocks, int64_t max_block_stages, int64_t traced,
+               int num_cu, int max_lds) {
+  const Layouts l = layouts(k, beta, gen, in, max_block_stages, traced, max_lds);
+  if (!l.one || (in != VIT_LLR_F32 && !fp32_integer_exact(beta, max_block_stages))) return -1;
+  return choose_kernel(k, beta, l, blocks, num_cu, max_lds);
+}
 
 hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsupported, const char **why) {
   *unsupported = 0;
@@ -374,9 +407,7 @@ hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsuppor
     const hipError_t err = device_info();
     if (err != hipSuccess) return err;
   }
-  // (a shape that one block a wave cannot hold is refused, whatever the others could)
-  const int64_t one = lds_bytes_per_block(a.k, a.beta, a.max_block_stages);
-  const bool several = a.nblocks > 1 && one <= t_dev.max_lds;
+  const Layouts l = layouts(a.k, a.beta, a.gen, a.llr_type, a.max_block_stages, a.sub_bits == 0 ? a.L + a.v2 : 0, t_dev.max_lds);
   if (a.llr_type != VIT_LLR_F32 && a.sub_bits == 0) {
     const int m = resolve_metric(a.k, a.beta, a.llr_type, a.metric_bits, a.max_block_stages, why);
     if (m < 0) {
@@ -384,13 +415,6 @@ hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsuppor
       return hipSuccess;
     }
     if (m == kMetric16) return launch_blocked16(a, stream, unsupported, why);
-    if (several) {
-      const int64_t traced = a.L + a.v2;
-      const int64_t mx = mx_takes(a.k, false) ? mx_lds_bytes(a.k, traced, false) : 0;
-      const int64_t quad = mx_takes(a.k, true) ? mx_lds_bytes(a.k, traced, true) : 0;
-      const IntKernel which = fastest(a.k, a.nblocks, one, mx, quad, t_dev.num_cu, t_dev.max_lds);
-      if (which != kOneBlock) return launch_blocked_mx(a, which == kQuad ? quad : mx, which == kQuad, stream);
-    }
   } else if (a.llr_type != VIT_LLR_F32) {
     // subframe traceback: the exact-in-fp32 integer kernels only
     if (a.metric_bits == kMetric16) {
@@ -403,9 +427,11 @@ hipError_t launch_blocked(const DecodeArgs &a, hipStream_t stream, int *unsuppor
       *why = "int8 block too long for exact integers in fp32";
       return hipSuccess;
     }
-  } else if (a.sub_bits == 0 && several && row_takes(a.k, a.beta, a.gen)) {
-    const int64_t lds = row_lds_bytes(a.k, a.L + a.v2);
-    if (row_is_faster(a.k, a.beta, a.nblocks, lds, t_dev.num_cu, t_dev.max_lds)) return launch_blocked_row(a, lds, stream);
+  }
+  switch (choose_kernel(a.k, a.beta, l, a.nblocks, t_dev.num_cu, t_dev.max_lds)) {
+    case VIT_KERNEL_MX16: return launch_blocked_mx(a, l.mx, false, stream);
+    case VIT_KERNEL_MX4: return launch_blocked_mx(a, l.quad, true, stream);
+    case VIT_KERNEL_ROW: return launch_blocked_row(a, l.row, stream);
   }
   const void *fn = a.llr_type != VIT_LLR_F32 && a.sub_bits == 0
                        ? pick_kernel_int(a.k, a.beta, a.gen, a.llr_type, false)
@@ -472,14 +498,13 @@ unsigned batch_launch_grid(const BatchLaunch &bl, int64_t count, int64_t max_blo
 }
 
 BatchGrid batch_grid_for(const BatchLaunch &bl, int64_t count, int64_t max_block_stages, bool whole_words) {
-  if (bl.row_fn && row_is_faster(bl.k, bl.beta, count, (int64_t)bl.row_lds, bl.num_cu, bl.max_lds))
-    return {bl.row_fn, row_grid(count), 64, bl.row_lds};
-  if (whole_words) {
-    const IntKernel which =
-        fastest(bl.k, count, (int64_t)bl.lds_words_per_wave * 4, (int64_t)bl.mx_lds[0], (int64_t)bl.mx_lds[1], bl.num_cu, bl.max_lds);
-    const bool quad = which == kQuad;
-    if (which != kOneBlock)
-      return {bl.mx_fn[quad], mx_grid(bl.k, count, (int64_t)bl.mx_lds[quad], bl.num_cu, bl.max_lds, quad), 64, bl.mx_lds[quad]};
+  const Layouts l = {(int64_t)bl.lds_words_per_wave * 4, whole_words ? (int64_t)bl.mx_lds[0] : 0,
+                     whole_words ? (int64_t)bl.mx_lds[1] : 0, (int64_t)bl.row_lds};
+  const int which = choose_kernel(bl.k, bl.beta, l, count, bl.num_cu, bl.max_lds);
+  if (which == VIT_KERNEL_ROW) return {bl.row_fn, row_grid(count), 64, bl.row_lds};
+  if (which != VIT_KERNEL_ONE_BLOCK) {
+    const bool quad = which == VIT_KERNEL_MX4;
+    return {bl.mx_fn[quad], mx_grid(bl.k, count, (int64_t)bl.mx_lds[quad], bl.num_cu, bl.max_lds, quad), 64, bl.mx_lds[quad]};
   }
   return {bl.fn, batch_launch_grid(bl, count, max_block_stages, bl.num_cu), bl.block, bl.lds};
 }
@@ -579,24 +604,18 @@ hipError_t plan_batch_launch(int k, int beta, const uint32_t *gen, int in, int m
   bl->lds_words_per_wave = (int)(lds_wave / 4);
   bl->items_per_wave = 1;
   bl->metric_bits = metric;
-  if (in == VIT_LLR_F32 && traced > 0 && row_takes(k, beta, gen) && row_lds_bytes(k, traced) <= t_dev.max_lds) {
-    bl->row_fn = pick_kernel_row(k, beta, true);
-    bl->row_lds = (size_t)row_lds_bytes(k, traced);
-    if (bl->row_lds > 65536) {
-      err = hipFuncSetAttribute(bl->row_fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bl->row_lds);
-      if (err != hipSuccess) return err;
-    }
-  }
+  const Layouts l = layouts(k, beta, gen, in, max_block_stages, traced, t_dev.max_lds);
+  if (l.row) bl->row_fn = pick_kernel_row(k, beta, true);
+  bl->row_lds = (size_t)l.row;
   for (const bool quad : {false, true}) {
-    if (in == VIT_LLR_F32 || traced <= 0 || !mx_takes(k, quad)) continue;
-    const int64_t need = mx_lds_bytes(k, traced, quad);
-    if (need > t_dev.max_lds) continue;
-    bl->mx_fn[quad] = pick_kernel_mx(k, beta, in, true, quad);
-    bl->mx_lds[quad] = (size_t)need;
-    if (need > 65536) {
-      err = hipFuncSetAttribute(bl->mx_fn[quad], hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
-      if (err != hipSuccess) return err;
-    }
+    bl->mx_lds[quad] = (size_t)(quad ? l.quad : l.mx);
+    if (bl->mx_lds[quad]) bl->mx_fn[quad] = pick_kernel_mx(k, beta, in, true, quad);
+  }
+  for (const auto &[other, need] : {std::pair{bl->row_fn, bl->row_lds}, std::pair{bl->mx_fn[0], bl->mx_lds[0]},
+                                    std::pair{bl->mx_fn[1], bl->mx_lds[1]}}) {
+    if (need <= 65536) continue;
+    err = hipFuncSetAttribute(other, hipFuncAttributeMaxDynamicSharedMemorySize, (int)need);
+    if (err != hipSuccess) return err;
   }
   return hipSuccess;
 }
