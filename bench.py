@@ -311,7 +311,6 @@ def bench_batched(vit, torch, args):
         "tuning": {BATCH_CODES[i]: {"L": t[0], "v": t[1], "waves_per_block": t[3]} for i, t in enumerate(tunes)},
         "ber_int8": err8 / nbits,
         "ber_fp32_same_shapes": err32 / nbits,
-        "tuning_tuples": [tuple(t) for t in tunes],
     }
 
 
@@ -781,11 +780,11 @@ def main():
         batched["int16"]["vs_stream_fp32"] = round(batched["int16"]["mbps"] / head["mbps"], 3)
     serving = None
     if not args.no_serving:
-        tunes = batched["tuning_tuples"] if batched else [(256, default_overlap(synth.CODES[c][0]), -1, 1)
-                                                          for c in BATCH_CODES]
+        # the server decodes one block a wave and its host works per block: long
+        # blocks, not the shapes that are fastest for a whole batch
+        tunes = [(256 if synth.CODES[c][0] > 7 else 512, default_overlap(synth.CODES[c][0]), -1, 1)
+                 for c in BATCH_CODES]
         serving = bench_serving(vit, torch, args, tunes)
-    if batched:
-        batched.pop("tuning_tuples", None)
     line = {
         "metric": METRIC,
         "value": round(head["mbps"], 2),

@@ -568,7 +568,9 @@ static int decode_batch_impl(vit_plan *plan, const vit_code *codes, int32_t ncod
 
 // Autotune (see vit.h).  Per code: decode the code's frames once with the
 // reference shape (L = 512, v1 = v2 = 128, far beyond the trellis's
-// convergence depth), then each candidate (L, v, waves) once; a candidate
+// convergence depth), then each candidate (L, v, waves) once (two waves a
+// workgroup only where the kernel that the block count selects has such
+// workgroups: between two runs of one launch the noise would choose); a candidate
 // whose decode differs from the reference in more than tune_tolerance of the
 // code's bits is rejected, the others are timed (3 runs) and the fastest is
 // kept.  The outputs are compared on the host.
@@ -634,7 +636,8 @@ static int plan_autotune_impl(vit_plan *plan, const vit_code *codes, int32_t nco
     float best_ms = 1e30f;
     for (int li = 0; li < 5 && result == VIT_OK; ++li) {
       for (size_t vi = 0; vi < vs.size() && result == VIT_OK; ++vi) {
-        for (int w = 1; w <= 2 && result == VIT_OK; ++w) {
+        bool by_waves = true;  // whether the kernel that runs this shape knows waves per workgroup
+        for (int w = 1; w <= (by_waves ? 2 : 1) && result == VIT_OK; ++w) {
           vit_tuning t;
           t.L = kL[li];
           t.v = vs[vi];
@@ -646,7 +649,11 @@ static int plan_autotune_impl(vit_plan *plan, const vit_code *codes, int32_t nco
             result = st;
             break;
           }
-          int64_t diff = 0;
+          int64_t blocks = 0, diff = 0;
+          bool whole = true;
+          (void)count_records(1, sub.data(), (int32_t)sub.size(), &t, &blocks);
+          vit::frames_of_whole_words(1, sub.data(), (int32_t)sub.size(), &whole);
+          by_waves = vit::batch_grid_for(plan->bl[0], blocks, (int64_t)t.L + t.v, whole).fn == plan->bl[0].fn;
           for (int64_t i = 0; i < out_bytes; ++i) diff += __builtin_popcount((unsigned)(ref[i] ^ cand[i]));
           if (diff > max_diff) continue;  // too far from the reference
           (void)hipEventRecord(e0, (hipStream_t)stream);
