@@ -118,9 +118,11 @@ typedef struct {
    * difference (eq. 3 in 16 bits; exact while compared metrics differ by less
    * than 2^15, which the spread bound (k-1)*2*128*beta + 2^14 guarantees);
    * blocks up to the LDS limit of two blocks' survivors per wave.  32: exact
-   * 32-bit integers; blocks up to 2^24 / (128 beta)
-   * stages.  0 (default): 32 where the blocks fit, else 16 (32 measured
-   * faster on gfx950).
+   * integers in 32-bit registers (int32; fp32 below 2^24, for many blocks of
+   * k = 8, 9 and with subframes: for many blocks less state 0's metric now and
+   * then, so that they stay there); blocks up to 2^24 / (128 beta) stages.
+   * 0 (default): 32 where the blocks fit, else 16 (32 measured faster on
+   * gfx950).
    * Subframe traceback runs with 32 only.  Ignored for FP32 LLRs. */
   int32_t metric_bits;
   uint64_t subframe_seed;   /* seed of VIT_SUBFRAME_RANDOM (default 0)         */

@@ -37,10 +37,11 @@
 //    load a lane brings 64 bytes of each row at k = 7 in the 4-register layout,
 //    and 16 in the other.
 //  * k <= 7: int8 LLRs straight from memory, 32-bit integer sums.  k = 8, 9
-//    need 2^P > 64, more than a byte's sign factor: fp16 operands, fp32 sums
-//    kept as 2^23 + 2^22 + integer, whose bits count like the integer's (the
-//    tags and the max work on the bits); the metrics are taken back towards 0
-//    every RENORM stages.
+//    need 2^P > 64, more than a byte's sign factor: fp16 operands (a byte and a
+//    power of two, both exact), fp32 sums kept as 2^23 + 2^22 + integer, whose
+//    bits count like the integer's (the tags and the max work on the bits); the
+//    metrics are taken back towards 0 every RENORM stages, so that each sum is
+//    the exact integer.
 //  * Blocks of different lengths share a wave: all end at the last stage of
 //    the last body; a block is set to its start metrics at its first stage (only
 //    the bodies in which some block starts look for it: a short last block of a
@@ -119,6 +120,11 @@ struct ShapeM {
   static constexpr int kRoom = ((1 << 22) >> P) - 1 - 256 * P * BETA;
   static constexpr int RENORM = kRoom / (128 * BETA) >= BODY ? BODY : kRoom / (128 * BETA) >= 2 * P ? 2 * P : P;
   static_assert(!F16 || kRoom >= 128 * BETA * RENORM, "fp32 sums leave their binade");
+  // A block that starts in state 0 n < P stages before its sums are taken back:
+  // its other states, 2^8 P beta + 1 below at the start, may have come down 2^7
+  // beta a stage and the reference up as much, and they come down further until
+  // every state is reached, P - n stages on (15873 of 16384 for k = 9, rate 1/4).
+  static_assert(!F16 || kRoom >= 128 * BETA * (2 * P - 1) + 1, "fp32 sums leave their binade after a start");
 };
 
 typedef const __attribute__((address_space(1))) uint8_t *gin_t;
