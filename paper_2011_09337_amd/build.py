@@ -4,6 +4,7 @@ Every call recompiles.  Sources are compiled in parallel (one hipcc per file),
 then linked into a shared library next to this file.
 """
 import os
+import re
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -28,9 +29,37 @@ COMMON = [
 ]
 
 
+def check_named_registers(asm):
+    """The matrix-core kernels keep survivor words in v128..v255 (4 metric
+    registers: v64..v127), which they move by asm that names them
+    (vit_decoder_mx.h): an instruction of the compiler's own on one of those, or
+    on an AGPR, would destroy them.  Raises RuntimeError if the assembly file
+    holds one."""
+    kernel, first, inside = None, 0, False
+    with open(asm) as f:
+        for line in f:
+            label = re.match(r"(\S*vit_\w+_(quad|mx)_kernel\S*):", line)
+            if label:
+                kernel, first = label.group(1), 64 if label.group(2) == "quad" else 128
+            elif "#ASMSTART" in line:
+                inside = True
+            elif "#ASMEND" in line:
+                inside = False
+            elif kernel and not inside and line.startswith("\t") and not line.strip().startswith((".", ";")):
+                code = line.split(";")[0]
+                regs = [int(x) for m in re.findall(r"\bv(?:(\d+)|\[(\d+):(\d+)\])", code) for x in m if x]
+                if any(r >= first for r in regs) or re.search(r"\ba(\d+|\[)", code):
+                    raise RuntimeError(f"{asm}: {kernel}: the compiler uses a register that the kernel names: {code.strip()}")
+    if kernel is None:
+        raise RuntimeError(f"{asm}: no matrix-core kernel found")
+
+
 def _compile(src, verbose):
     obj = os.path.join(BUILD_DIR, os.path.basename(src) + ".o")
     lang = ["-x", "hip"] if src.endswith(".hip") else ["-x", "hip"]
+    mx = src.startswith("vit_kernels_mx")
+    if mx:
+        lang = ["-save-temps=obj"] + lang
     cmd = [HIPCC] + COMMON + lang + ["-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
@@ -42,6 +71,8 @@ def _compile(src, verbose):
         raise RuntimeError(f"hipcc failed for {src}:\n{msg}")
     if msg and verbose:
         print(msg)
+    if mx:
+        check_named_registers(os.path.join(BUILD_DIR, f"{os.path.splitext(src)[0]}-hip-amdgcn-amd-amdhsa-{ARCH}.s"))
     return obj
 
 
