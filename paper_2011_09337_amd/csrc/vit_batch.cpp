@@ -370,7 +370,9 @@ int ensure_staging(vit_plan *p, int slot, size_t bytes) {
   }
   size_t cap = 1 << 16;
   while (cap < bytes) cap *= 2;
-  hipError_t e = hipHostMalloc(&p->staging[slot], cap, hipHostMallocDefault);
+  // coherent: the work list kernel reads the records in place, and the host
+  // rewrites the slot every other call
+  hipError_t e = hipHostMalloc(&p->staging[slot], cap, hipHostMallocMapped | hipHostMallocCoherent);
   if (e != hipSuccess) return vit::api_fail_hip(e, "hipHostMalloc");
   p->staging_cap[slot] = cap;
   return VIT_OK;
