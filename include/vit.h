@@ -194,7 +194,8 @@ int vit_query_geometry(const vit_code *code, int64_t n, int32_t L, int32_t v, in
  * possibly of different codes and lengths, decoded in one call: a kernel writes
  * the work list (one item per block, longest first) on the device from one
  * record per frame, then one kernel per code (in sequence, most work per bit
- * first) walks its items, wave w of W taking items w, w + W, w + 2W, ...
+ * first) walks its items, each wave one or (where there are many) a tile of 2 to
+ * 64 neighbours at a time.
  * Results are identical, bit for bit, to decoding each frame alone with
  * vit_decode_ex and the same (L, v, v1). */
 

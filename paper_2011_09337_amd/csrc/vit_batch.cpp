@@ -1,5 +1,5 @@
 // vit_batch.cpp -- batched decoding of many frames (mixed codes and lengths):
-// work lists, one reusable hipGraph per plan, and the autotuner.
+// work lists, the launches of a call, and the autotuner.
 //
 // A batch is cut into blocks exactly as each frame would be on its own
 // (Sec. III of the paper, per frame).  Each block is one work item; items of

@@ -631,8 +631,8 @@ __device__ __forceinline__ void trace_tile(D_ &D, const Blk &bk, uint32_t uc, in
 }
 
 // Decode NB blocks; lane tau < NB describes block tau (lanes above: any block
-// again).  The caller guarantees windows of at least P stages that lie in
-// memory from `before` bytes ahead on.
+// again).  The caller guarantees windows that lie in memory from `before` bytes
+// ahead on and, with those bytes, hold at least four.
 // `describe` is called before the recursion and again after it, which costs
 // less than holding its result in registers.
 template <int K, int BETA, int IN, bool QUAD, class Describe>

@@ -130,14 +130,6 @@ hipError_t device_info() {
   return hipSuccess;
 }
 
-// Resolve the integer metric width for a decode of blocks of at most
-// max_block_stages stages: the 16-bit kernels where asked for, the
-// exact-in-fp32 integer kernels where asked for or (auto) where their bound
-// and their survivor storage allow, else (auto) the 16-bit kernels where two
-// blocks' survivors fit a workgroup's LDS.  Auto prefers the 32-bit kernels
-// because they measured faster on gfx950 (the 16-bit kernels hold two
-// blocks' survivors per wave, which halves the waves the LDS admits).
-// -1 = no kernel (why is set).
 void *pick_kernel_row(int k, int beta, bool batch) {
   switch (k) {
     case 3: return pick_kernel_row_k3(beta, batch);
@@ -148,6 +140,13 @@ void *pick_kernel_row(int k, int beta, bool batch) {
   return nullptr;
 }
 
+// Resolve the integer metric width for a decode of blocks of at most
+// max_block_stages stages: the 16-bit kernels where asked for, the 32-bit
+// integer kernels where asked for or (auto) where their bound and the one-block
+// kernel's survivor storage allow, else (auto) the 16-bit kernels where two
+// blocks' survivors fit a workgroup's LDS.  Auto prefers 32 bits, which measured
+// faster (8192 int8 frames of three codes 0.36 ms, with 16-bit
+// metrics 1.00).  -1 = no kernel (why is set).
 int resolve_metric(int k, int beta, int in, int metric_bits, int64_t max_block_stages, const char **why) {
   if (in == VIT_LLR_F32) return 0;
   const bool fits16 = lds16_bytes_per_wave(k, beta, max_block_stages) <= t_dev.max_lds;
@@ -241,9 +240,11 @@ int mx_waves_per_cu(int64_t lds, int max_lds, bool quad) {
 // K=6, L = 256, 4096 blocks 20 / 35 / 19, 65536 209 / 49 / 60; K=5, L = 256,
 // 4096 blocks 20 / - / 18, 65536 204 / - / 34; K=3, L = 256, 4096 blocks
 // 22 / - / 24, 16384 58 / - / 25; K=9, L = 256, 1024 blocks 26 / 38 / -,
-// 4096 66 / 48 / -, 16384 237 / 94 / -.  Over nine lengths and thirteen sizes
-// of seven codes the choice took at most 6 % more than the best but at L = 2048
-// (K=4 r1/4 37 %) and where two were within 10 %.
+// 4096 66 / 48 / -, 16384 237 / 94 / -.  Over eight lengths (64 to 2048) and
+// thirteen sizes of eight codes the choice took 0.2 % more than the best in the
+// mean, and more than 10 % at eight: K=3, 4 and 7 r1/3 with 2900 to 4096 long
+// blocks (to 15 %), K=6 at L = 320, 2^24 bits (13 %), K=7 at L = 64, 4096 blocks
+// (18 %), K=8 at L = 512, 4096 blocks (13 %), K=9 at L = 768, 1366 blocks (14 %).
 //
 // One block a wave: one wave's latency, and 10.6 for each further 64 states on
 // a SIMD; in rounds where LDS (lds: a block's) holds fewer than four waves a SIMD.
@@ -322,7 +323,9 @@ int64_t row_lds_bytes(int k, int64_t traced) {
 // four a wave): K=5 r1/2, L = 256, 4096 blocks 22 / 18, 16384 63 / 27, 65536
 // 214 / 82; K=5, L = 512, 2048 blocks 23 / 28, 4096 37 / 29; K=6 r1/2, L = 256,
 // 4096 blocks 23 / 25, 8192 36 / 28, 65536 221 / 130; K=6 r1/3, L = 512, 32768
-// blocks 226 / 129; K=3 r1/2, L = 256, 3104 blocks 21 / 21, 65536 204 / 83.
+// blocks 226 / 129; K=3 r1/2, L = 256, 3104 blocks 21 / 21, 65536 204 / 83.  Over
+// the lengths and sizes above the choice took at most 6 % more than the better one
+// but for K=6 r1/3 at L = 2048, 4096 blocks (208 / 147).
 bool row_is_faster(int k, int beta, int64_t blocks, int64_t lds, int num_cu, int max_lds) {
   const int64_t unit = (lds + 1279) / 1280 * 1280, by_lds = max_lds / unit;
   const double fit = by_lds < 16 ? (double)by_lds / 4 : 4.0;
